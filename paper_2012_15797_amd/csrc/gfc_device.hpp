@@ -264,6 +264,40 @@ __device__ __forceinline__ float stamp_lane1(float v) {
   }
 }
 
+// v plus the value that the DPP control CTRL brings to this lane.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+
+// Sum over each aligned group of N lanes (N = 16, 32 or 64); every lane of
+// the group receives the total.  Fixed order, the same in every lane, and no
+// LDS: adds with DPP operands within a row of 16 lanes (pairs, quads, halves,
+// the row), then the swaps of rows and of wavefront halves.
+template <int N>
+__device__ __forceinline__ float lane_sum(float v) {
+  static_assert(N == 16 || N == 32 || N == 64, "16, 32 or 64 lanes");
+  v = dpp_add<0xB1>(v);   // quad_perm 1, 0, 3, 2
+  v = dpp_add<0x4E>(v);   // quad_perm 2, 3, 0, 1
+  v = dpp_add<0x141>(v);  // row_half_mirror
+  v = dpp_add<0x140>(v);  // row_mirror
+  if constexpr (N >= 32) {
+    unsigned a = __builtin_bit_cast(unsigned, v), b = a;
+    asm volatile("" : "+v"(b));  // a register of its own: the swap writes both
+    const auto s = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    const unsigned s0 = s[0], s1 = s[1];
+    v = __builtin_bit_cast(float, s0) + __builtin_bit_cast(float, s1);
+  }
+  if constexpr (N >= 64) {
+    unsigned a = __builtin_bit_cast(unsigned, v), b = a;
+    asm volatile("" : "+v"(b));
+    const auto s = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    const unsigned s0 = s[0], s1 = s[1];
+    v = __builtin_bit_cast(float, s0) + __builtin_bit_cast(float, s1);
+  }
+  return v;
+}
+
 // Value of v in lane k of the wavefront (k uniform).
 __device__ __forceinline__ float lane_f(float v, int k) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), k));

@@ -14,11 +14,10 @@ namespace gfc {
 template <int W>
 hipError_t launch_render_small(const RenderArgs& args, hipStream_t stream);
 
-// Forward render, W = 256 (device scratch allocated stream-ordered per call).
+// Forward render, W = 256.
 hipError_t launch_render_w256(const RenderArgs& args, hipStream_t stream);
 
-// Adjoint, W = 256: per-stamp parameter gradients and amplitude partials
-// (device scratch allocated stream-ordered per call).
+// Adjoint, W = 256: per-stamp parameter gradients and amplitude partials.
 hipError_t launch_bwd_w256(const RenderArgs& args, const float* gout, float* grad_params, float* amp_part,
                            hipStream_t stream);
 
