@@ -36,7 +36,6 @@ SOURCES = [
     "render_w256.hip",
     "render_bwd.hip",
     "render_bwd_w256.hip",
-    "lanczos.hip",
     "sersic.hip",
     "psf_fft.hip",
     "serve.cpp",

@@ -73,6 +73,9 @@ struct Galaxy {
   bool ok;
 };
 
+// Four floats in memory that are aligned as floats are.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+
 __device__ __forceinline__ bool finitef(float v) { return __builtin_isfinite(v); }
 
 // Step 3: C_i = v_i B with B = A A^T, A = CD^{-1} E.  With c^2, s^2 and cs of
@@ -262,6 +265,15 @@ __device__ __forceinline__ float stamp_lane1(float v) {
   } else {
     return __shfl(v, ((int)__lane_id() & ~(W - 1)) + 1, 64);
   }
+}
+
+// The value held by the next lower (upper) lane of the wavefront, zero in the
+// first (last) lane: DPP wave shifts by one.
+__device__ __forceinline__ float lane_below(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_above(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
 }
 
 // v plus the value that the DPP control CTRL brings to this lane.

@@ -38,7 +38,6 @@
 namespace gfc {
 
 // The upstream gradient is only promised to be aligned as floats are.
-typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef const __attribute__((address_space(1))) v4f_any* GlobalF4;
 
 __global__ void __launch_bounds__(w256::BLOCK)

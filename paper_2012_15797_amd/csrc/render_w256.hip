@@ -21,7 +21,8 @@
 //                  transform (the pair step, a 16-point FFT in registers, a
 //                  radix-8 stage through the wavefront's LDS slice), add the
 //                  real-space components (step 8) to their 32 pixels and
-//                  store them.
+//                  store them; with the Lanczos-3 shift the half's pixels go
+//                  to LDS instead, are filtered there and then stored.
 #include <atomic>
 
 #include "gfc_device.hpp"
@@ -57,9 +58,12 @@ __device__ __forceinline__ uint32_t stamp_word(const RenderArgs& p, int64_t g, i
 // LDS: the first wavefront forms them once and every wavefront reads them.
 constexpr int kGalWords = 16;
 
-// From the stamp's input words, word i held by lane i of the wavefront.
-template <int W>
-__device__ __forceinline__ void publish_galaxy(const RenderArgs& p, uint32_t word, int lane, uint32_t* s_gal) {
+// From the stamp's input words, word i held by lane i of the wavefront.  LZ:
+// with the normalised Lanczos weights of its sub-pixel shift, taps d = -3..2
+// along x, then along y, in s_lw[12].
+template <int W, bool LZ>
+__device__ __forceinline__ void publish_galaxy(const RenderArgs& p, uint32_t word, int lane, uint32_t* s_gal,
+                                               float* s_lw) {
   uint32_t w[7];
   static_for<0, 7>([&](auto ii) {
     constexpr int i = decltype(ii)::value;
@@ -69,6 +73,16 @@ __device__ __forceinline__ void publish_galaxy(const RenderArgs& p, uint32_t wor
                                               __builtin_bit_cast(float, w[2]), __builtin_bit_cast(float, w[3]),
                                               __builtin_bit_cast(float, w[4]), __builtin_bit_cast(float, w[5]),
                                               (int)w[6]});
+  if constexpr (LZ) {
+    const float v = __builtin_bit_cast(float, lane < 6 ? w[0] : w[1]);
+    const float raw = lane < 12 ? lanczos3((float)((lane % 6) - 3) + (v - floorf(v))) : 0.f;
+    float sx = 0.f, sy = 0.f;
+    static_for<0, 6>([&](auto dd) {
+      sx += lane_f(raw, decltype(dd)::value);
+      sy += lane_f(raw, 6 + decltype(dd)::value);
+    });
+    if (lane < 12) s_lw[lane] = raw * (1.f / (lane < 6 ? sx : sy));
+  }
   const float lamq = -kQ * shape_min_eig(G);
   if (lane == 0) {
     uint4* d = reinterpret_cast<uint4*>(s_gal);
@@ -108,16 +122,21 @@ __device__ __forceinline__ Galaxy read_galaxy(const uint32_t* s_gal, float* lamq
 
 // EIG: spatially varying PSF (eigen-PSF components with polynomial weights).
 // PT: each galaxy names its constant PSF in p.psf_id (serving batches).
+// LZ: the Lanczos-3 sub-pixel shift (the galaxy sits at its integer position).
 //
 // Persistent: the resident workgroups (one per CU: the LDS holds one half of
 // a stamp) take stamps in turn.  Lanes 0..9 of the first wavefront load the
 // inputs of a workgroup's next stamp while it renders the current one, so a
 // stamp starts without a memory round trip, and the first wavefront forms
 // the next stamp's galaxy for all sixteen.
-template <bool EIG, bool PT>
+template <bool EIG, bool PT, bool LZ>
 __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa) {
   using namespace w256;
-  __shared__ float2 s_buf[LDS_F2];
+  __shared__ __attribute__((aligned(16))) float2 s_buf[LDS_F2];
+  // LZ: the last five rows of the first half, for the rows of the second that
+  // need them; the weights
+  __shared__ __attribute__((aligned(16))) float s_top[LZ ? 5 * W : 1];
+  __shared__ float s_lw[12];
   __shared__ float2 s_py[W + 2];
   __shared__ float2 s_nyq[W];
   __shared__ float s_tw[NC];        // the Nyquist row's omega = -1/2 twin, per column
@@ -133,7 +152,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
   {
     const uint32_t w0 = threadIdx.x < kInWords ? stamp_word<EIG, PT>(pa, blockIdx.x, threadIdx.x) : 0u;
     if (threadIdx.x < kInWords) s_in[threadIdx.x] = w0;
-    if (threadIdx.x < 64) publish_galaxy<W>(pa, w0, (int)threadIdx.x, s_gal);
+    if (threadIdx.x < 64) publish_galaxy<W, LZ>(pa, w0, (int)threadIdx.x, s_gal, s_lw);
   }
   if (threadIdx.x < 256) {
     const int hh = threadIdx.x >> 5, kg = threadIdx.x & 31;  // kg = 8 k + g
@@ -155,6 +174,14 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
   });
   float lamq_pub;
   Galaxy G = read_galaxy(s_gal, &lamq_pub);
+  float wx[6], wy[6];  // Lanczos weights, in scalar registers
+  if constexpr (LZ) {
+    static_for<0, 6>([&](auto dd) {
+      constexpr int d = decltype(dd)::value;
+      wx[d] = uniform_f(s_lw[d]);
+      wy[d] = uniform_f(s_lw[6 + d]);
+    });
+  }
   // PSF spectra are global memory (the pointer read from the PSF table would
   // otherwise be generic and its loads flat, which also count as LDS waits)
   GlobalF2 psfm = (GlobalF2)p.psf_main;
@@ -537,6 +564,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
         });
       }
     }
+    if constexpr (!LZ) {
     // eight lanes store one 128-byte segment of the row
     float* orow = outp + (int64_t)y * W + 4 * r;
     const bool acc = (p.flags & kAccumulate) != 0;
@@ -547,12 +575,71 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
       if (acc) val += *dst;
       __builtin_nontemporal_store(val, dst);
     });
+    } else {
+      // Lanczos-3 shift of the finished pixels.  The half's rows go to LDS,
+      // each into its wavefront's own slots of s_buf (row stride 2 TS = 260
+      // floats: the eight lanes of a 16-byte access fall in distinct banks),
+      // and are filtered along y, then along x, a wavefront to a row and four
+      // columns to a lane: the neighbours along x are the next lanes'.  Rows
+      // and columns outside the stamp are zeros.  Rows 126 and 127 wait for
+      // the second half, which keeps rows 123..127 of the first in s_top.
+      // 2,000 stamps take 293 us (the plain render 252 us); with a pass of its
+      // own over the stamps in memory they took 490 us.
+      float* tile = reinterpret_cast<float*>(s_buf);
+      {
+        float* trow = tile + yloc * (2 * TS) + 4 * r;
+        static_for<0, 8>([&](auto qq) {
+          constexpr int q = decltype(qq)::value;
+          const v4f val = {zq[0][q].x, zq[0][q].y, zq[1][q].x, zq[1][q].y};
+          *reinterpret_cast<v4f*>(trow + 32 * q) = val;
+          if (half == 0 && yloc >= HROWS - 5) *reinterpret_cast<v4f*>(s_top + (yloc - (HROWS - 5)) * W + 4 * r + 32 * q) = val;
+        });
+      }
+      __syncthreads();
+      int l4;  // this lane's columns 4 lane .. 4 lane + 3, renewed
+      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l4));
+      auto row4 = [&](int y) -> v4f {  // four pixels of row y (y uniform)
+        if (y < 0 || y >= W) return v4f{0.f, 0.f, 0.f, 0.f};
+        if (half == 1 && y < HROWS) return *reinterpret_cast<const v4f*>(s_top + (y - (HROWS - 5)) * W + 4 * l4);
+        return *reinterpret_cast<const v4f*>(tile + (y - half * HROWS) * (2 * TS) + 4 * l4);
+      };
+      auto shift_rows = [&](auto nn, int y0) {  // output rows y0 .. y0 + N - 1
+        constexpr int N = decltype(nn)::value;
+        v4f in[N + 5];
+        static_for<0, N + 5>([&](auto ii) { in[decltype(ii)::value] = row4(y0 - 3 + decltype(ii)::value); });
+        static_for<0, N>([&](auto ii) {
+          constexpr int i = decltype(ii)::value;
+          v4f a = {0.f, 0.f, 0.f, 0.f};
+          static_for<0, 6>([&](auto dd) {
+            static_for<0, 4>([&](auto jj) {
+              constexpr int d = decltype(dd)::value, j = decltype(jj)::value;
+              a[j] = fmaf(wy[d], in[i + d][j], a[j]);
+            });
+          });
+          // columns 4 lane - 3 .. 4 lane + 5
+          const float e[9] = {lane_below(a[1]), lane_below(a[2]), lane_below(a[3]), a[0], a[1],
+                              a[2],             a[3],             lane_above(a[0]), lane_above(a[1])};
+          v4f o;
+          static_for<0, 4>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            float h = 0.f;
+            static_for<0, 6>([&](auto dd) { h = fmaf(wx[decltype(dd)::value], e[j + decltype(dd)::value], h); });
+            o[j] = h;
+          });
+          __builtin_nontemporal_store(o, reinterpret_cast<v4f*>(outp + (int64_t)(y0 + i) * W + 4 * l4));
+        });
+      };
+      const int y0 = half * HROWS + 8 * wv;
+      shift_rows(std::integral_constant<int, 6>{}, y0);
+      if (half == 1 || wv < NWAVE - 1) shift_rows(std::integral_constant<int, 2>{}, y0 + 6);
+      if (half == 1 && wv == NWAVE / 2) shift_rows(std::integral_constant<int, 2>{}, HROWS - 2);
+    }
   });
   if (!G.ok && t == 0) atomicAdd(p.invalid, 1ull);
   // every thread read s_in and s_gal at this stamp's start, before the
   // barriers above
   if (t < kInWords) s_in[t] = in_next;
-  if (wv == 0) publish_galaxy<W>(p, in_next, lane, s_gal);
+  if (wv == 0) publish_galaxy<W, LZ>(p, in_next, lane, s_gal, s_lw);
   }  // stamps of this workgroup
 }
 
@@ -560,7 +647,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
 // (one per CU), queried once per device.
 // (Launches from several host threads may fill an entry at once; they store
 // the same value.)
-template <bool EIG, bool PT>
+template <bool EIG, bool PT, bool LZ>
 static hipError_t w256_resident(int64_t* out) {
   constexpr int kMaxDev = 64;
   static std::atomic<int64_t> cached[kMaxDev];
@@ -573,7 +660,7 @@ static hipError_t w256_resident(int64_t* out) {
     int cus = 0, per = 0;
     e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, render_w256_kernel<EIG, PT>, w256::BLOCK, 0);
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, render_w256_kernel<EIG, PT, LZ>, w256::BLOCK, 0);
     if (e != hipSuccess) return e;
     v = (int64_t)std::max(per, 1) * std::max(cus, 1);
     cached[dev].store(v, std::memory_order_relaxed);
@@ -582,20 +669,26 @@ static hipError_t w256_resident(int64_t* out) {
   return hipSuccess;
 }
 
-template <bool EIG, bool PT>
+template <bool EIG, bool PT, bool LZ>
 static hipError_t launch_w256(const RenderArgs& args, hipStream_t stream) {
   if (args.n <= 0) return hipSuccess;
   int64_t resident = 0;
-  hipError_t e = w256_resident<EIG, PT>(&resident);
+  hipError_t e = w256_resident<EIG, PT, LZ>(&resident);
   if (e != hipSuccess) return e;
   const int64_t nb = std::min<int64_t>(args.n, resident);
-  hipLaunchKernelGGL((render_w256_kernel<EIG, PT>), dim3((unsigned)nb), dim3(w256::BLOCK), 0, stream, args);
+  hipLaunchKernelGGL((render_w256_kernel<EIG, PT, LZ>), dim3((unsigned)nb), dim3(w256::BLOCK), 0, stream, args);
   return hipGetLastError();
 }
 
 hipError_t launch_render_w256(const RenderArgs& args, hipStream_t stream) {
-  if (args.psf_id) return args.eig_J > 0 ? hipErrorInvalidValue : launch_w256<false, true>(args, stream);
-  return args.eig_J > 0 ? launch_w256<true, false>(args, stream) : launch_w256<false, false>(args, stream);
+  const bool lz = (args.flags & kLanczos3) != 0;
+  if (args.psf_id) {
+    if (args.eig_J > 0) return hipErrorInvalidValue;
+    return lz ? launch_w256<false, true, true>(args, stream) : launch_w256<false, true, false>(args, stream);
+  }
+  if (args.eig_J > 0)
+    return lz ? launch_w256<true, false, true>(args, stream) : launch_w256<true, false, false>(args, stream);
+  return lz ? launch_w256<false, false, true>(args, stream) : launch_w256<false, false, false>(args, stream);
 }
 
 }  // namespace gfc

@@ -77,6 +77,33 @@ def test_lanczos_edge_positions(ctx, W):
     psf.close(); mix.close()
 
 
+@pytest.mark.parametrize("W,n", [(128, 8), (256, 8), (256, 520)])
+def test_lanczos_in_the_tile_edges(ctx, W, n):
+    """The shift of the finished half stamp in LDS (128 and 256): centres near
+    and beyond the edges and next to the seam between the halves, with
+    real-space components, into an `out` aligned as floats only (128).  520
+    stamps of 256 are two to three per resident workgroup: every copy of a
+    galaxy must equal its first rendering bit for bit."""
+    import torch
+    import paper_2012_15797_amd as gfc
+
+    cfg = wl.config_metric(8)
+    base = cfg["gal"]
+    xs = np.tile(np.array([0.3, 63.6, -2.4, 65.7, 31.9, 31.25, 62.1, 1.5]) * (W / 64), n // 8).astype(np.float32)
+    ys = np.tile(np.array([0.6, 63.2, 31.9, -1.8, 32.1, 30.7, 0.2, 66.4]) * (W / 64), n // 8).astype(np.float32)
+    rep = lambda a: np.tile(a, n // 8)
+    gal = wl.Galaxies(xs, ys, rep(base.flux), rep(base.r_e * np.float32(W / 16)), rep(base.e1), rep(base.e2),
+                      rep(base.mix_id), np.full(n, W, np.int32))
+    psf, mix = lib_objects(ctx, cfg)
+    off = 1 if W == 128 else 0
+    out = torch.empty(n * W * W + off, device="cuda")[off:].view(n, W, W)
+    gfc.gfc_render_stamps(ctx, psf, mix, gal.x, gal.y, gal.flux, gal.r_e, gal.e1, gal.e2, W, flags=LZ, out=out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out[:8].repeat(n // 8, 1, 1))
+    _check(out[:8].cpu().numpy().astype(np.float64), oracle_lanczos(cfg, gal, range(8)), range(8))
+    psf.close(); mix.close()
+
+
 @pytest.mark.parametrize("extra", [1, 2])
 def test_lanczos_with_forced_routing(ctx, extra):
     rng = np.random.Generator(np.random.PCG64(950 + extra))
