@@ -35,7 +35,7 @@ SOURCES = [
     "render_fwd.hip",
     "render_w256.hip",
     "render_bwd.hip",
-    "render_bwd_w256.hip",
+    "render_bwd_split.hip",
     "sersic.hip",
     "psf_fft.hip",
     "serve.cpp",

@@ -10,7 +10,7 @@ namespace gfc {
 
 // Contributions of mixture component k to the chain rule (dx, dy, dF and the
 // three entries of dL/dB), and its amplitude partial written to ap[k].
-// pk_sum[k * pk_stride]: the component's Fourier sum p_k; racc[6 k + i]: its
+// pk_sum[k * pk_stride]: the component's Fourier sum p_k; racc[k racc_stride + i]: its
 // real-space sums (sum g N, g N z_x, g N z_y, g N z_x^2, g N z_x z_y, g N z_y^2).
 struct CompTerms {
   float dx, dy, dF, L11, L12, L22;
@@ -19,7 +19,7 @@ struct CompTerms {
 template <int W>
 __device__ inline CompTerms bwd_component_terms(const RenderArgs& p, const Galaxy& G, int k, unsigned rmask,
                                                 const float* pk_sum, int pk_stride, const float* racc,
-                                                float* ap) {
+                                                int racc_stride, float* ap) {
   CompTerms c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (k >= G.K) {
     ap[k] = 0.f;
@@ -38,7 +38,7 @@ __device__ inline CompTerms bwd_component_terms(const RenderArgs& p, const Galax
   const float pk = pk_sum[k * pk_stride];
   float g0 = 0.f;
   if (rmask & (1u << k)) {
-    const float* R = racc + 6 * k;
+    const float* R = racc + racc_stride * k;
     g0 = R[0];
     const float sxx = fmaf(v, G.b11, p.pg[2]);
     const float sxy = fmaf(v, G.b12, p.pg[3]);
@@ -64,18 +64,15 @@ __device__ inline CompTerms bwd_component_terms(const RenderArgs& p, const Galax
   return c;
 }
 
-// Sum of CompTerms over each group of 16 lanes (fixed butterfly order); every
+// Sum of CompTerms over each group of 16 lanes (fixed order); every
 // lane of the group receives the totals.  Called with every lane active.
 __device__ __forceinline__ CompTerms sum16(CompTerms c) {
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) {
-    c.dx += __shfl_xor(c.dx, o);
-    c.dy += __shfl_xor(c.dy, o);
-    c.dF += __shfl_xor(c.dF, o);
-    c.L11 += __shfl_xor(c.L11, o);
-    c.L12 += __shfl_xor(c.L12, o);
-    c.L22 += __shfl_xor(c.L22, o);
-  }
+  c.dx = lane_sum<16>(c.dx);
+  c.dy = lane_sum<16>(c.dy);
+  c.dF = lane_sum<16>(c.dF);
+  c.L11 = lane_sum<16>(c.L11);
+  c.L12 = lane_sum<16>(c.L12);
+  c.L22 = lane_sum<16>(c.L22);
   return c;
 }
 

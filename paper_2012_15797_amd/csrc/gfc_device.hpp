@@ -282,17 +282,19 @@ __device__ __forceinline__ float dpp_add(float v) {
   return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
 
-// Sum over each aligned group of N lanes (N = 16, 32 or 64); every lane of
+// Sum over each aligned group of N lanes (N = 4, 16, 32 or 64); every lane of
 // the group receives the total.  Fixed order, the same in every lane, and no
 // LDS: adds with DPP operands within a row of 16 lanes (pairs, quads, halves,
 // the row), then the swaps of rows and of wavefront halves.
 template <int N>
 __device__ __forceinline__ float lane_sum(float v) {
-  static_assert(N == 16 || N == 32 || N == 64, "16, 32 or 64 lanes");
-  v = dpp_add<0xB1>(v);   // quad_perm 1, 0, 3, 2
-  v = dpp_add<0x4E>(v);   // quad_perm 2, 3, 0, 1
-  v = dpp_add<0x141>(v);  // row_half_mirror
-  v = dpp_add<0x140>(v);  // row_mirror
+  static_assert(N == 4 || N == 16 || N == 32 || N == 64, "4, 16, 32 or 64 lanes");
+  v = dpp_add<0xB1>(v);  // quad_perm 1, 0, 3, 2
+  v = dpp_add<0x4E>(v);  // quad_perm 2, 3, 0, 1
+  if constexpr (N >= 16) {
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    v = dpp_add<0x140>(v);  // row_mirror
+  }
   if constexpr (N >= 32) {
     unsigned a = __builtin_bit_cast(unsigned, v), b = a;
     asm volatile("" : "+v"(b));  // a register of its own: the swap writes both

@@ -1,5 +1,6 @@
-// Adjoint of the forward render for W = 16, 32, 64, 128 (Lang 2020, Section
-// 2, steps 3-8, differentiated).
+// Adjoint of the forward render for W = 16 and 32 (Lang 2020, Section 2, steps
+// 3-8, differentiated), the amplitude reductions and the adjoint's entry
+// points.
 //
 // For a loss L with upstream gradient g = dL/dI, the Fourier-path part is
 // evaluated in the frequency domain:
@@ -14,7 +15,8 @@
 // real-space part is accumulated pixel by pixel.  Per-component sums feed the
 // amplitude gradients and the routing-weight terms of the smooth ramp.
 //
-// Each stamp is handled by W lanes, as in the forward kernel:
+// Each stamp is handled by W lanes, as in the forward kernel (W = 64 and up
+// take the kernel of render_bwd_split.hip):
 //  load        lane = output column: real-space sums, g un-rolled into LDS
 //  row R2C     lane = row: real-to-complex forward transform (W/2-point FFT)
 //  column DFT  lane (c, h): decimation in frequency, rows k_y = 2m + h
@@ -33,191 +35,136 @@ namespace gfc {
 
 template <int W>
 struct BwdCfg {
+  static_assert(W == 16 || W == 32, "several stamps per wavefront");
   static constexpr int M = W / 2;
-  static constexpr int BLOCK = W < 64 ? 64 : W;
+  static constexpr int BLOCK = 64;
   static constexpr int SPB = BLOCK / W;
   static constexpr int TS = W + 2;            // floats per row of the g tile / float2 per row of Gr is W/2+1
   static constexpr int TN = W * (W + 2);      // floats per stamp
   // Floats from one stamp's tile to the next.  At W = 16 two stamps share
   // each 32-lane half of a wavefront, whose 4-byte LDS accesses are served
   // together: a stride of 16 (mod 32) puts the two stamps in different banks.
-  static constexpr int TNP = W < 32 ? TN + 16 : TN;
-  static constexpr int CH = W <= 64 ? W : 32; // rows per load chunk
+  static constexpr int TNP = W < 32 ? TN + 80 : TN;
   static constexpr int NP = M + 3;            // evaluation points per lane
-  // points per block of the component loop: 35 points in blocks of 12, 12, 11 at 64 (blocks
-  // of 18 spill), 67 in blocks of 23, 22, 22 at 128 (in the accumulation registers there;
-  // one block of 67 spills to memory)
-  static constexpr int PB = M <= 16 ? NP : (W == 128 ? 23 : 12);
-  static constexpr int WPE = W == 16 ? 3 : (W <= 64 ? 2 : 1);  // occupancy target (waves per SIMD)
+  // Points per block of the component loop: 10 and 9 at 32 x 32, so that the
+  // kernel keeps within 128 registers and four wavefronts per SIMD (one block
+  // of 19 takes 184 registers and two).
+  static constexpr int PB = W == 32 ? 10 : NP;
+  // p_k partials [kKmax][PKS] in the tile, once the column DFT has read it:
+  // the row stride W + LPK makes their reduction free of bank conflicts.
+  static constexpr int LPK = W / kKmax;  // lanes per component in that reduction
+  static constexpr int PKS = W + LPK;
+  // behind them the packed Nyquist column and the phases
+  static constexpr int NYQ = (kKmax * PKS + 1) / 2, PY = NYQ + W;  // float2
+  static_assert(W % kKmax == 0 && 2 * (PY + W + 2) <= TNP, "the overlays fit in the tile");
 };
 
-// Sum over the W lanes of one stamp; every lane of the stamp receives the total.
-// Fixed butterfly order (deterministic).  For W = 128 the two wavefronts meet
-// in LDS.
 template <int W>
-__device__ __forceinline__ float seg_sum(float v, float* s_x2) {
-  constexpr int LIM = W < 64 ? W : 64;
-#pragma unroll
-  for (int o = 1; o < LIM; o <<= 1) v += __shfl_xor(v, o);
-  if constexpr (W == 128) {
-    const int wv = (threadIdx.x >> 6) & 1;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) s_x2[wv] = v;
-    __syncthreads();
-    v = s_x2[0] + s_x2[1];
-  }
-  return v;
-}
-
-// Five such sums with one meeting in LDS for W = 128.
-template <int W>
-__device__ __forceinline__ void seg_sum5(float& a, float& b, float& c, float& d, float& e, float* s_x10) {
-  constexpr int LIM = W < 64 ? W : 64;
-#pragma unroll
-  for (int o = 1; o < LIM; o <<= 1) {
-    a += __shfl_xor(a, o);
-    b += __shfl_xor(b, o);
-    c += __shfl_xor(c, o);
-    d += __shfl_xor(d, o);
-    e += __shfl_xor(e, o);
-  }
-  if constexpr (W == 128) {
-    const int wv = (threadIdx.x >> 6) & 1;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-      s_x10[wv] = a;
-      s_x10[2 + wv] = b;
-      s_x10[4 + wv] = c;
-      s_x10[6 + wv] = d;
-      s_x10[8 + wv] = e;
-    }
-    __syncthreads();
-    a = s_x10[0] + s_x10[1];
-    b = s_x10[2] + s_x10[3];
-    c = s_x10[4] + s_x10[5];
-    d = s_x10[6] + s_x10[7];
-    e = s_x10[8] + s_x10[9];
-  }
-}
-
-template <int W>
-__global__ void __launch_bounds__(BwdCfg<W>::BLOCK) __attribute__((amdgpu_waves_per_eu(BwdCfg<W>::WPE)))
+__global__ void __launch_bounds__(BwdCfg<W>::BLOCK) __attribute__((amdgpu_waves_per_eu(4)))
 render_bwd_small_kernel(RenderArgs p, const float* __restrict__ gout, float* __restrict__ grad_params,
                         float* __restrict__ amp_part) {
   using C = BwdCfg<W>;
   constexpr int M = C::M;
   constexpr int NP = C::NP;
   constexpr int TS = C::TS;
-  __shared__ float s_tile[C::SPB][C::TNP];
-  __shared__ float2 s_py[C::SPB][W + 2];
-  __shared__ float2 s_nyq[C::SPB][W];
+  __shared__ __attribute__((aligned(8))) float s_tile[C::SPB][C::TNP];
   __shared__ float s_racc[C::SPB][kKmax][6];
   __shared__ float4 s_cmp[C::SPB][kKmax];  // per component: v, w A, w A v (zero when unused)
-  __shared__ float s_x2[10];
 
-  // with one stamp per workgroup the stamp index is uniform (scalar)
-  const int l = C::SPB == 1 ? (int)threadIdx.x : (int)threadIdx.x % W;
-  const int slot = C::SPB == 1 ? 0 : (int)threadIdx.x / W;
+  const int l = (int)threadIdx.x % W;
+  const int slot = (int)threadIdx.x / W;
   const int64_t stamp = (int64_t)blockIdx.x * C::SPB + slot;
   const bool live = stamp < p.n;
   const int64_t gidx = live ? stamp : p.n - 1;
-  Galaxy G = load_galaxy<W>(p, gidx);
-  if constexpr (C::SPB == 1) {
-    make_uniform(G);
-  }
+  const Galaxy G = load_galaxy<W>(p, gidx);
   const float* amp = p.amp + G.table * kKmax;
   const float* var = p.var + G.table * kKmax;
   const float trB = G.b11 + G.b22;
-  const int kloop = (C::SPB == 1) ? G.K : p.kmax;
+  const int kloop = p.kmax;
 
   // per-component constants of the Fourier sums, computed once per stamp:
   // v, w A, w A v and w (w = 0 past the table's K).  A component with A = 0
   // still needs its sums: dL/dA does not depend on A.
-  bool real_share = false;  // lane k < K of each wavefront: component k has a real-space share
+  bool real_share = false;  // lane k < K of the stamp: component k has a real-space share
   {
-    const int k = l & 63;
+    const int k = l;
     if (k < kKmax) {
       const float v = var[k];
       const bool in = k < G.K;
       const float w = in ? route_weight<W>(v * trB, p.flags) : 0.f;
       const float wa = w * (in ? amp[k] : 0.f);
-      if (l < kKmax) s_cmp[slot][l] = make_float4(v, wa, wa * v, w);
+      s_cmp[slot][k] = make_float4(v, wa, wa * v, w);
       real_share = in && w < 1.f;
     }
   }
 
   // routing: components with a real-space share (whatever their amplitude),
-  // from the lanes' weights
-  unsigned rmask = 0;
-  if constexpr (C::SPB == 1) {
-    rmask = (unsigned)__ballot(real_share) & ((1u << kKmax) - 1u);
-  } else {  // this stamp's W lanes of the ballot
-    const unsigned long long rb = __ballot(real_share);
-    rmask = (unsigned)(rb >> ((int)__lane_id() & ~(W - 1))) & ((1u << kKmax) - 1u);
-  }
+  // from the lanes' weights (this stamp's W lanes of the ballot)
+  const unsigned rmask = (unsigned)(__ballot(real_share) >> ((int)__lane_id() & ~(W - 1))) & ((1u << kKmax) - 1u);
 
   // ------------------------------------------------------------ load + real space
   const float* gp = gout + gidx * (int64_t)(W * W);
   float* tile = s_tile[slot];
+  float2* s_nyq = reinterpret_cast<float2*>(tile) + C::NYQ;
+  float2* s_py = reinterpret_cast<float2*>(tile) + C::PY;
   {
     const float dx = (float)l - G.x0 - p.pg[0];
     const int coldst = (l - G.nx) & (W - 1);
-    for (int k = 0; k < kKmax; ++k) {
-      if (l < 6) s_racc[slot][k][l] = 0.f;
-    }
-    for (int r0 = 0; r0 < W; r0 += C::CH) {
-      float gv[C::CH];
-      static_for<0, C::CH>([&](auto rr) {
+    float gv[W];
+    static_for<0, W>([&](auto rr) {
+      constexpr int r = decltype(rr)::value;
+      gv[r] = gp[r * W + l];
+      tile[((r - G.ny) & (W - 1)) * TS + coldst] = gv[r];
+    });
+    for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
+      const int k = __builtin_ctz(mk);
+      const float v = var[k];
+      const float sxx = fmaf(v, G.b11, p.pg[2]);
+      const float sxy = fmaf(v, G.b12, p.pg[3]);
+      const float syy = fmaf(v, G.b22, p.pg[4]);
+      const float det = fmaf(sxx, syy, -(sxy * sxy));
+      const float rdet = __builtin_amdgcn_rcpf(det);
+      const float ixy = -sxy * rdet, iyy = sxx * rdet;
+      const float nrm = kInv2Pi * __builtin_amdgcn_rsqf(det);
+      const float dy0 = -G.y0 - p.pg[1];
+      // Along this lane's column, z = S^-1 (dx, dy) has zy = ixy dx + iyy dy
+      // and zx = al + be zy with al = dx / sxx, be = -sxy / sxx, and the
+      // quadratic form is q = dx al + zy^2 / iyy.  So the column needs the
+      // moments sum g N zy^p (p = 0, 1, 2) only, with the log2 of
+      // nrm exp(-q/2) as c0 + c2 zy^2 (the normalisation folded in).
+      const float rsxx = __builtin_amdgcn_rcpf(sxx);
+      const float al = dx * rsxx, be = -sxy * rsxx;
+      const float zy0 = fmaf(iyy, dy0, ixy * dx);
+      const float c0 = fmaf(kHalfLog2e * al, dx, __builtin_amdgcn_logf(nrm));
+      const float c2 = kHalfLog2e * __builtin_amdgcn_rcpf(iyy);
+      float m0 = 0.f, m1 = 0.f, m2 = 0.f;
+      static_for<0, W>([&](auto rr) {
         constexpr int r = decltype(rr)::value;
-        gv[r] = gp[(r0 + r) * W + l];
-        tile[((r0 + r - G.ny) & (W - 1)) * TS + coldst] = gv[r];
+        const float zy = fmaf(iyy, (float)r, zy0);
+        const float zz = zy * zy;
+        const float gn = gv[r] * __builtin_amdgcn_exp2f(fmaf(c2, zz, c0));
+        m0 += gn;
+        m1 = fmaf(gn, zy, m1);
+        m2 = fmaf(gn, zz, m2);
       });
-      for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
-        const int k = __builtin_ctz(mk);
-        const float v = var[k];
-        const float sxx = fmaf(v, G.b11, p.pg[2]);
-        const float sxy = fmaf(v, G.b12, p.pg[3]);
-        const float syy = fmaf(v, G.b22, p.pg[4]);
-        const float det = fmaf(sxx, syy, -(sxy * sxy));
-        const float rdet = __builtin_amdgcn_rcpf(det);
-        const float ixy = -sxy * rdet, iyy = sxx * rdet;
-        const float nrm = kInv2Pi * __builtin_amdgcn_rsqf(det);
-        const float dy0 = (float)r0 - G.y0 - p.pg[1];
-        // Along this lane's column, z = S^-1 (dx, dy) has zy = ixy dx + iyy dy
-        // and zx = al + be zy with al = dx / sxx, be = -sxy / sxx, and the
-        // quadratic form is q = dx al + zy^2 / iyy.  So the column needs the
-        // moments sum g N zy^p (p = 0, 1, 2) only, with the log2 of
-        // nrm exp(-q/2) as c0 + c2 zy^2 (the normalisation folded in).
-        const float rsxx = __builtin_amdgcn_rcpf(sxx);
-        const float al = dx * rsxx, be = -sxy * rsxx;
-        const float zy0 = fmaf(iyy, dy0, ixy * dx);
-        const float c0 = fmaf(kHalfLog2e * al, dx, __builtin_amdgcn_logf(nrm));
-        const float c2 = kHalfLog2e * __builtin_amdgcn_rcpf(iyy);
-        float m0 = 0.f, m1 = 0.f, m2 = 0.f;
-        static_for<0, C::CH>([&](auto rr) {
-          constexpr int r = decltype(rr)::value;
-          const float zy = fmaf(iyy, (float)r, zy0);
-          const float gn = gv[r] * __builtin_amdgcn_exp2f(fmaf(c2 * zy, zy, c0));
-          const float gz = gn * zy;
-          m0 += gn;
-          m1 += gz;
-          m2 = fmaf(gz, zy, m2);
-        });
-        // sum g N (1, zx, zy, zx^2, zx zy, zy^2) from the moments
-        float a0 = m0, ay = m1, ayy = m2;
-        float ax = fmaf(be, m1, al * m0);
-        float axy = fmaf(be, m2, al * m1);
-        float axx = fmaf(be, axy, al * ax);
-        a0 = seg_sum<W>(a0, s_x2);
-        seg_sum5<W>(ax, ay, axx, axy, ayy, s_x2);
-        if (l == 0) {
-          s_racc[slot][k][0] += a0;
-          s_racc[slot][k][1] += ax;
-          s_racc[slot][k][2] += ay;
-          s_racc[slot][k][3] += axx;
-          s_racc[slot][k][4] += axy;
-          s_racc[slot][k][5] += ayy;
-        }
+      // sum g N (1, zx, zy, zx^2, zx zy, zy^2) from the moments
+      float a0 = m0, ay = m1, ayy = m2;
+      float ax = fmaf(be, m1, al * m0);
+      float axy = fmaf(be, m2, al * m1);
+      float axx = fmaf(be, axy, al * ax);
+      a0 = lane_sum<W>(a0);
+      ax = lane_sum<W>(ax);
+      ay = lane_sum<W>(ay);
+      axx = lane_sum<W>(axx);
+      axy = lane_sum<W>(axy);
+      ayy = lane_sum<W>(ayy);
+      if (l == 0) {
+        s_racc[slot][k][0] = a0;
+        s_racc[slot][k][1] = ax;
+        s_racc[slot][k][2] = ay;
+        s_racc[slot][k][3] = axx;
+        s_racc[slot][k][4] = axy;
+        s_racc[slot][k][5] = ayy;
       }
     }
   }
@@ -272,28 +219,24 @@ render_bwd_small_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
     });
     fft<M, -1>(Gk);
   }
-  // Unpack the packed column: Z = G0 + i GN, with G0 and GN Hermitian in k_y.
+  // The Nyquist column is taken out of the packed one, Z = G0 + i GN with G0
+  // and GN Hermitian in k_y.  It need not be taken away from column 0: every
+  // sum over the bins below is the real part of a sum of terms that are
+  // Hermitian in k_y there, to which i times another such column adds nothing.
+  __syncthreads();  // the tile has been read
   if (c == 0) {
     static_for<0, M>([&](auto mm) {
       constexpr int m = decltype(mm)::value;
-      s_nyq[slot][2 * m + h] = Gk[m];
+      s_nyq[2 * m + h] = Gk[m];
     });
   }
   __syncthreads();
   float2 GN;  // 2 G[k_y = l][W/2]
   {
-    const float2 za = s_nyq[slot][l], zb = cconj(s_nyq[slot][(W - l) & (W - 1)]);
+    const float2 za = s_nyq[l], zb = cconj(s_nyq[(W - l) & (W - 1)]);
     const float2 d = csub(za, zb);
     GN = make_float2(0.5f * d.y, -0.5f * d.x);  // (za - conj zb) / (2 i)
   }
-  if (c == 0) {
-    static_for<0, M>([&](auto mm) {
-      constexpr int m = decltype(mm)::value;
-      const float2 zb = cconj(s_nyq[slot][(W - 2 * m - h) & (W - 1)]);
-      Gk[m] = cscale(cadd(Gk[m], zb), 0.5f);
-    });
-  }
-
   // ------------------------------------------------------------ phases and U0 per point
   const float nu = (float)c * (1.f / W);
   const float hW = (float)h * (1.f / W);
@@ -305,8 +248,8 @@ render_bwd_small_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
   sincospi_poly(h ? -G.fx : -2.f * G.fx * nu, &sxa, &cxa);
   const float sx = pair_even(sxa), cx = pair_even(cxa);
   const float sxh = stamp_lane1<W>(sxa), cxh = stamp_lane1<W>(cxa);
-  s_py[slot][l] = make_float2(cy, sy);
-  if (l == W / 2) s_py[slot][W] = make_float2(cy, -sy);  // omega = -1/2: conjugate of omega = +1/2
+  s_py[l] = make_float2(cy, sy);
+  if (l == W / 2) s_py[W] = make_float2(cy, -sy);  // omega = -1/2: conjugate of omega = +1/2
   __syncthreads();
 
   // Points: m = 0..M-1 (column c, row 2m+h), M (omega = -1/2 twin of the
@@ -340,18 +283,19 @@ render_bwd_small_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
       const float2 gp2 = cmul(cmulc(P, Gk[m]), px);   // P conj(G) x phase x weight
       float2 u;
       if constexpr (2 * m == W / 2) {
-        const float2 q0 = s_py[slot][W / 2 + h];
+        const float2 q0 = s_py[W / 2 + h];
         const float2 pyA = h ? q0 : cscale(q0, 0.5f);
         u = cmul(gp2, pyA);
-        const float2 pyB = h ? make_float2(0.f, 0.f) : cscale(s_py[slot][W], 0.5f);
+        const float2 pyB = h ? make_float2(0.f, 0.f) : cscale(s_py[W], 0.5f);
         const float2 ux = cmul(gp2, pyB);
         ure[M] = ux.x;
         uim[M] = ux.y;
       } else {
-        u = cmul(gp2, s_py[slot][2 * m + h]);
+        u = cmul(gp2, s_py[2 * m + h]);
       }
       ure[m] = u.x;
       uim[m] = u.y;
+      asm volatile("" : "+v"(ure[m]), "+v"(uim[m]));  // formed here, not sunk to its uses with its operands held
       if constexpr (m % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // bounds the PSF loads in flight
     });
     // Nyquist column, row l: h = 1, halved for the factor 2 in GN, and the
@@ -374,14 +318,8 @@ render_bwd_small_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
 
   // ------------------------------------------------------------ component loop
   float ax = 0.f, ay = 0.f, a11 = 0.f, a12 = 0.f, a22 = 0.f;
-  // per-lane p_k partials [kKmax][PKS] in the g tile, which the column DFT
-  // has finished reading.  The row stride W + LPK makes the reduction below
-  // free of bank conflicts.
-  constexpr int LPK = W / kKmax;  // lanes per component in that reduction
-  static_assert(LPK >= 1 && W % kKmax == 0, "components share the stamp's lanes evenly");
-  constexpr int PKS = W + LPK;
-  float* s_pk = &s_tile[slot][0];
-  static_assert(kKmax * PKS <= C::TN, "p_k partials fit in the tile");
+  constexpr int LPK = C::LPK, PKS = C::PKS;
+  float* s_pk = tile;  // per-lane p_k partials
   for (int k = 0; k < kKmax; ++k) s_pk[k * PKS + l] = 0.f;
   float m_si = 0.f, m_csi = 0.f, m_r = 0.f, m_cr = 0.f, m_ccr = 0.f;
   // The exponent's quadratic form along this lane's column, expanded about
@@ -483,7 +421,11 @@ render_bwd_small_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
   a11 = fmaf(nu * nu, m_r, a11);
   a12 = fmaf(nu, fmaf(hW, m_r, m_cr), a12);
   a22 += fmaf(hW, fmaf(hW, m_r, 2.f * m_cr), m_ccr);
-  seg_sum5<W>(ax, ay, a11, a12, a22, s_x2);
+  ax = lane_sum<W>(ax);
+  ay = lane_sum<W>(ay);
+  a11 = lane_sum<W>(a11);
+  a12 = lane_sum<W>(a12);
+  a22 = lane_sum<W>(a22);
   __syncthreads();
   // p_k = sum over the stamp's W partials, fixed order: LPK lanes per
   // component, lane i taking the entries i, i + LPK, ..., then a butterfly
@@ -507,13 +449,11 @@ render_bwd_small_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
     // values, so that neither it nor its addresses hold registers through
     // the loops above.
     const RenderArgs& pc = kernel_args_renewed<RenderArgs>();
-    int64_t gi = gidx;
-    if constexpr (C::SPB == 1) asm volatile("" : "+s"(gi));
-    Galaxy Gc = load_galaxy<W>(pc, gi);
-    if constexpr (C::SPB == 1) make_uniform(Gc);
+    const int64_t gi = gidx;
+    const Galaxy Gc = load_galaxy<W>(pc, gi);
     CompTerms t = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (live && l < kKmax)
-      t = bwd_component_terms<W>(pc, Gc, l, rmask, s_pk, PKS, &s_racc[slot][0][0], amp_part + gi * kKmax);
+      t = bwd_component_terms<W>(pc, Gc, l, rmask, s_pk, PKS, &s_racc[slot][0][0], 6, amp_part + gi * kKmax);
     t = sum16(t);
     if (l == 0 && live) bwd_chain_finish<W>(pc, Gc, gi, ax, ay, a11, a12, a22, t, grad_params);
   }
@@ -745,9 +685,7 @@ gfc_status gfc_render_stamps_backward(gfc_ctx* ctx, gfc_psf* psf, const gfc_mix*
   switch (W) {
     case 16: e = launch_bwd_small<16>(a, grad_out, gp, amp_part, s); break;
     case 32: e = launch_bwd_small<32>(a, grad_out, gp, amp_part, s); break;
-    case 64: e = launch_bwd_small<64>(a, grad_out, gp, amp_part, s); break;
-    case 128: e = launch_bwd_small<128>(a, grad_out, gp, amp_part, s); break;
-    case 256: e = launch_bwd_w256(a, grad_out, gp, amp_part, s); break;
+    default: e = launch_bwd_split(a, W, grad_out, gp, amp_part, s); break;
   }
   if (e == hipSuccess && grad_amp)
     e = launch_amp_grad(amp_part, gal->mix_id, n, mix->n_tables, grad_amp, ws + (size_t)n * (kKmax + 6), s);
@@ -787,8 +725,7 @@ gfc_status gfc_render_stamps_backward_noalloc(gfc_ctx* ctx, gfc_psf* psf, const 
   switch (W) {
     case 16: e = launch_bwd_small<16>(a, grad_out, gp, amp_part, s); break;
     case 32: e = launch_bwd_small<32>(a, grad_out, gp, amp_part, s); break;
-    case 64: e = launch_bwd_small<64>(a, grad_out, gp, amp_part, s); break;
-    case 128: e = launch_bwd_small<128>(a, grad_out, gp, amp_part, s); break;
+    default: e = launch_bwd_split(a, W, grad_out, gp, amp_part, s); break;
   }
   if (e == hipSuccess && grad_amp)
     e = launch_amp_grad(amp_part, gal->mix_id, n, mix->n_tables, grad_amp, ws + (size_t)n * (kKmax + 6), s,

@@ -59,26 +59,28 @@ def test_backward_w256_across_chunks(ctx):
     psf.close(); mix.close()
 
 
+@pytest.mark.parametrize("W", [32, 64, 128, 256])
 @pytest.mark.parametrize("case", ["positions", "skip", "sheared"])
-def test_backward_w256_routes(ctx, case):
-    """The on-chip 256 x 256 adjoint where its parts can go wrong: centres on
-    integers of either parity, negative and outside the stamp (the integer
-    part is a phase, its sign the Nyquist column's); the skip of negligible
-    blocks at its extremes (r_e 2 and 60 px, |e| = 0.69 at four orientations);
-    a sheared CD matrix with a 16-component table, and an upstream gradient
-    that is aligned as floats only."""
+def test_backward_routes(ctx, case, W):
+    """The adjoint where its parts can go wrong: centres on integers of either
+    parity, negative and outside the stamp (from 64 up the integer part is a
+    phase, its sign the Nyquist column's); the skip of negligible blocks at
+    its extremes (r_e W/128 and W/4 px, |e| = 0.69 at four orientations); a
+    sheared CD matrix with a 16-component table, and an upstream gradient that
+    is aligned as floats only."""
     import torch
     import paper_2012_15797_amd as gfc
 
-    rng = np.random.Generator(np.random.PCG64(320))
+    rng = np.random.Generator(np.random.PCG64(320 + W))
     cfg = wl.config_metric(10)
-    W, n, cd, mix_src = 256, 8, None, cfg["mix"].as_f32()
-    gal = wl.draw_galaxies(rng, n, W, 0, r_e_range=(2.0, 60.0))
+    n, cd, mix_src = 8, None, cfg["mix"].as_f32()
+    gal = wl.draw_galaxies(rng, n, W, 0, r_e_range=(W / 128, W / 4))
     if case == "positions":
-        gal.x[:] = [128, 127, 0, -3.25, 255.5, 300.75, 129.5, 64]
-        gal.y[:] = [127, 128, 255.25, 40, -1.5, 131, 0.75, 192]
+        h = W // 2
+        gal.x[:] = [h, h - 1, 0, -3.25, W - 0.5, W + 2.75, h + 1.5, h / 2]
+        gal.y[:] = [h - 1, h, W - 0.75, 5, -1.5, h + 3, 0.75, 1.5 * h]
     elif case == "skip":
-        gal.r_e[:] = np.repeat([2.0, 60.0], 4)
+        gal.r_e[:] = np.repeat([W / 128, W / 4], 4)
         gal.e1[:], gal.e2[:] = np.tile([0.69, -0.69, 0, 0], 2), np.tile([0, 0, 0.69, -0.69], 2)
     else:
         cd = np.array([1.3, 0.4, -0.5, 0.8], np.float32)
@@ -94,8 +96,8 @@ def test_backward_w256_routes(ctx, case):
                                             cd=cd)
     torch.cuda.synchronize()
     rp, ra, ra_abs = oracle_grads(cfg, gal, g, cd=None if cd is None else cd.astype(np.float64), mix=mix_src)
-    assert_close(gp.cpu().numpy(), rp, f"params W=256 {case}")
-    assert_close(ga.cpu().numpy(), ra, f"amplitudes W=256 {case}", scale=ra_abs)
+    assert_close(gp.cpu().numpy(), rp, f"params W={W} {case}")
+    assert_close(ga.cpu().numpy(), ra, f"amplitudes W={W} {case}", scale=ra_abs)
     psf.close(); mix.close()
 
 
