@@ -317,6 +317,69 @@ __device__ __forceinline__ float lane_f(float v, int k) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), k));
 }
 
+// A uniform value in a vector register.  An instruction with a scalar operand
+// issues every 4.2 cycles per SIMD; with vector operands two wavefronts issue
+// together, every 2.3 cycles.
+__device__ __forceinline__ float vector_f(float v) {
+  float r;
+  asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
+  return r;
+}
+
+// 2^x on -1 <= x <= 0 as a polynomial with value 1 at 0: the minimax fit of
+// degree 6, error 1.5e-9 (a fit in double precision, coefficients rounded).
+constexpr int kFlatDeg = 6;
+constexpr float kFlat[kFlatDeg + 1] = {1.f,           0x1.62e42cp-1f,  0x1.ebfaeep-3f, 0x1.c697c8p-5f,
+                                       0x1.39fd70p-7f, 0x1.4ee1c4p-10f, 0x1.cd1ae6p-14f};
+
+// The flat components of a stamp: those whose exponent v q stays within one
+// power of two over the whole frequency grid (|v q| <= v qmax <= 1, qmax the
+// largest |q|, at a corner of the grid: q is a convex quadratic form).  Their
+// sum is one polynomial in x = q / qmax,
+//   sum_k w_k A_k 2^(v_k q) = sum_j a_j x^j,  a_j = kFlat[j] sum_k w_k A_k (v_k qmax)^j,
+// seven multiply-adds per bin instead of a multiply, an exponential and a
+// multiply-add for each of them (an exponential issues every 8.2 cycles, a
+// multiply-add beside it every 4: 16.6 cycles per component and bin, against
+// about 17 for the polynomial).  Of eight components log-spaced over 1e-4..10
+// r_e^2, four are flat at r_e = 2 px, two at 8 px.
+struct FlatSum {
+  float a[kFlatDeg + 1];
+  float s;  // 1 / qmax
+  __device__ __forceinline__ float at(float q) const {
+    const float x = q * s;
+    float r = fmaf(a[kFlatDeg], x, a[kFlatDeg - 1]);
+    static_for<2, kFlatDeg + 1>([&](auto jj) { r = fmaf(r, x, a[kFlatDeg - decltype(jj)::value]); });
+    return r;
+  }
+};
+
+// Lane k of each group of N lanes holds component k's variance vk and Fourier
+// amplitude wak (w A; zero past the table's K).  With two or more flat
+// components in a stamp (one costs the same either way), their amplitudes
+// move from wak into the sums f (every lane of the group); returns whether
+// the lane's stamp has such a sum.  N = 64: f in vector registers.
+template <int N>
+__device__ __forceinline__ bool take_flat(const Galaxy& G, float vk, float& wak, FlatSum& f) {
+  const float qmax = fmaxf(-kQ * fmaf(0.25f, G.b11 + G.b22, 0.5f * fabsf(G.b12)), 1e-30f);
+  const float t = vk * qmax;
+  bool flat = t <= 1.f && wak != 0.f && finitef(wak);
+  const unsigned long long b = __ballot(flat) >> ((int)__lane_id() & ~(N - 1) & 63);
+  const bool any = __popcll(b & (N == 64 ? ~0ull : (1ull << (N & 63)) - 1ull)) >= 2;
+  flat = flat && any;
+  f.s = __builtin_amdgcn_rcpf(qmax);
+  float p = flat ? wak : 0.f;
+  static_for<0, kFlatDeg + 1>([&](auto jj) {
+    constexpr int j = decltype(jj)::value;
+    // N = 64: the components are in the first row of 16 lanes
+    float a = kFlat[j] * lane_sum<(N == 64 ? 16 : N)>(p);
+    if constexpr (N == 64) a = vector_f(lane_f(a, 0));
+    f.a[j] = a;
+    p *= t;
+  });
+  if (flat) wak = 0.f;
+  return any;
+}
+
 // Raw Lanczos-3 value at t (exact zeros at the integers other than 0), for
 // the optional pixel-space sub-pixel shift (Section 2, step 8).
 __device__ __forceinline__ float lanczos3(float t) {

@@ -311,8 +311,9 @@ render_small_kernel(RenderArgs p) {
   };
   if constexpr (kPsfFirst) psf_terms();
 
-  // Component 0 initialises the sums (every table has one; with zero Fourier
-  // weight it contributes zeros), the rest accumulate.
+  // The flat components' polynomial initialises the sums, or the first
+  // component with a Fourier share (with none, component 0 contributes zeros);
+  // the rest accumulate.
   float S[M + 1];
   float SN[2];
   unsigned rmask = 0;  // components with a real-space share
@@ -325,6 +326,10 @@ render_small_kernel(RenderArgs p) {
       constexpr int j = decltype(jj)::value;
       SN[j] = wa * __builtin_amdgcn_exp2f(v * qn[j]);
     });
+  };
+  auto flat_terms = [&](const FlatSum& f) {
+    static_for<0, M + 1>([&](auto mm) { S[decltype(mm)::value] = f.at(qv[decltype(mm)::value]); });
+    static_for<0, NQ>([&](auto jj) { SN[decltype(jj)::value] = f.at(qn[decltype(jj)::value]); });
   };
   auto add_terms = [&](float v, float wa) {
     static_for<0, M + 1>([&](auto mm) {
@@ -351,11 +356,19 @@ render_small_kernel(RenderArgs p) {
       if (rk && l == lk) s_rs[slot][lk] = make_float2(vk, (1.f - wk) * Ak);
     }
     rmask = (unsigned)__ballot(rk);
-    first_terms(lane_f(vk, 0), lane_f(wak, 0));
-    for (int k = 1; k < G.K; ++k) {
-      const float wa = lane_f(wak, k);
-      if ((__builtin_bit_cast(unsigned, wa) << 1) == 0u) continue;  // w A = +-0
-      add_terms(lane_f(vk, k), wa);
+    FlatSum f;
+    const bool flat = take_flat<64>(G, vk, wak, f);  // uniform
+    unsigned mk = (unsigned)__ballot(wak != 0.f);
+    if (flat) {
+      flat_terms(f);
+    } else {
+      const int k = mk ? __builtin_ctz(mk) : 0;
+      first_terms(vector_f(lane_f(vk, k)), vector_f(lane_f(wak, k)));
+      mk &= mk - 1;
+    }
+    for (; mk != 0; mk &= mk - 1) {
+      const int k = __builtin_ctz(mk);
+      add_terms(vector_f(lane_f(vk, k)), vector_f(lane_f(wak, k)));
     }
   } else {
     // Several stamps per wavefront: lane k of each stamp works out its
@@ -373,8 +386,10 @@ render_small_kernel(RenderArgs p) {
     }
     const unsigned long long rb = __ballot(rk);
     rmask = (unsigned)(rb >> ((int)__lane_id() & ~(W - 1))) & (unsigned)((1ull << W) - 1ull);
-    first_terms(__shfl(vk, 0, W), __shfl(wak, 0, W));
-    for (int k = 1; k < kloop; ++k) {
+    FlatSum f;
+    take_flat<W>(G, vk, wak, f);
+    flat_terms(f);
+    for (int k = 0; k < kloop; ++k) {
       const float wa = __shfl(wak, k, W);
       if (wa == 0.f) continue;
       add_terms(__shfl(vk, k, W), wa);

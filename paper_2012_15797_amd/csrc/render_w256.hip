@@ -285,7 +285,6 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
   const float vmaxN = uniform_f(kSkipLog2 * __builtin_amdgcn_rcpf(lamq * 0.25f));  // |nu| = 1/2 or |omega| = 1/2
   float S[M];
   float SN[3] = {0.f, 0.f, 0.f};
-  static_for<0, M>([&](auto mm) { S[decltype(mm)::value] = 0.f; });
   // Lane k of every wavefront works out component k's route weight (K <= 16
   // lanes), the loop takes v and w A from it by lane reads, and lane k of
   // the first wavefront forms the component's real-space constants.
@@ -314,20 +313,27 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
     }
   }
   const unsigned rmask = (unsigned)__ballot(rk) & ((1u << kKmax) - 1u);
-  for (int k = 0; k < G.K; ++k) {
-    const float wa = lane_f(wak, k);
-    if (wa == 0.f) continue;
-    const float v = lane_f(vk, k);
+  FlatSum f;
+  if (take_flat<64>(G, vk, wak, f)) {  // uniform
+    static_for<0, M>([&](auto mm) { S[decltype(mm)::value] = f.at(qv[decltype(mm)::value]); });
+    if (nyq) static_for<0, 3>([&](auto jj) { SN[decltype(jj)::value] = f.at(qn[decltype(jj)::value]); });
+  } else {
+    static_for<0, M>([&](auto mm) { S[decltype(mm)::value] = 0.f; });
+  }
+  for (unsigned mk = (unsigned)__ballot(wak != 0.f); mk != 0; mk &= mk - 1) {
+    const int k = __builtin_ctz(mk);
+    const float vs = lane_f(vk, k);  // compared as an integer (both positive): a scalar compare
+    const float wa = vector_f(lane_f(wak, k)), v = vector_f(vs);
     static_for<0, M / 8>([&](auto bb) {
       constexpr int b = decltype(bb)::value;
-      if (v < vmax[b]) {
+      if (__builtin_bit_cast(int, vs) < __builtin_bit_cast(int, vmax[b])) {
         static_for<0, 8>([&](auto ii) {
           constexpr int m = 8 * b + decltype(ii)::value;
           S[m] = fmaf(wa, __builtin_amdgcn_exp2f(v * qv[m]), S[m]);
         });
       }
     });
-    if (nyq && v < vmaxN) {
+    if (nyq && __builtin_bit_cast(int, vs) < __builtin_bit_cast(int, vmaxN)) {
       SN[0] = fmaf(wa, __builtin_amdgcn_exp2f(v * qn[0]), SN[0]);
       SN[1] = fmaf(wa, __builtin_amdgcn_exp2f(v * qn[1]), SN[1]);
       if (twin) SN[2] = fmaf(wa, __builtin_amdgcn_exp2f(v * qn[2]), SN[2]);
