@@ -16,10 +16,11 @@
 //                is applied while reading back.
 //  row phase     lane y owns row y and runs the length-W complex-to-real
 //                inverse transform as a W/2-point complex FFT in registers.
-//  store         rows go through LDS with the integer part of the x centre
-//                applied as a cyclic roll (the integer part of y is a phase
-//                in the y-phase table), then real-space components (step 8)
-//                are added and stamps are written coalesced.
+//  store         real-space components (step 8) are added to the row in its
+//                lane's registers, and half a stamp at a time goes through LDS
+//                to memory, four pixels per lane.
+// The integer parts of the centre enter the phases as exact table entries, so
+// the stamp leaves the transforms in output order.
 #include "gfc_device.hpp"
 #include "gfc_launch.hpp"
 
@@ -39,6 +40,9 @@ struct SmallCfg {
   static constexpr int T1S = W / 2 + 1;          // float2 per row: W/4 columns x 2 halves + pad
   static constexpr int T1N = M * T1S;            // float2 per stamp; also (W/2) x (W+1) floats
   static constexpr int HR = W / 2;               // rows of the store tile per pass
+  // Floats per row of the store tile: 16-byte aligned, and 4 (mod 32) or the
+  // like, so that the eight rows of a 16-byte access fall in distinct banks.
+  static constexpr int LSO = W + 4;
 };
 
 // EIG: the PSF varies over the image (eigen-PSF components with polynomial
@@ -60,16 +64,15 @@ render_small_kernel(RenderArgs p) {
   // output order, at 128 x 128 on the finished half stamp in the LDS tile.
   constexpr bool LZF = LZ && W <= 64, LZT = LZ && W == 128;
   constexpr int LS = W + 8;  // floats per row of the LZT tile: four zero pixels on each side
-  constexpr int T1N = LZT ? (C::HR + 2) * LS / 2 : C::T1N;
-  static_assert(T1N >= C::T1N, "the transposes fit");
+  constexpr int T1N = LZT ? (C::HR + 2) * LS / 2 : C::HR * C::LSO / 2;
+  static_assert(T1N >= C::T1N && T1N % 2 == 0, "the transposes fit");
   __shared__ __attribute__((aligned(16))) float2 s_t1[C::SPB][T1N];  // 16-byte aligned: also read as float4
   __shared__ float2 s_py[C::SPB][W + 2];
   __shared__ float2 s_nyq[C::SPB][W];
-  __shared__ float2 s_rs[C::SPB][kKmax];  // (v, (1 - w) A) of the components with a real-space share
-  // per real-space component, its column constants (g, amplitude, -sxy / sxx,
-  // log2(e) / (2 sxx)) of the store below (not with the shift on the rows)
-  __shared__ float4 s_rc[C::SPB][LZF ? 1 : kKmax];
-  __shared__ float s_lw[C::SPB][LZT ? 24 : 12];  // raw Lanczos weights of the stamp, per wavefront
+  // per real-space component, its row constants (amplitude, g, sxy / syy,
+  // -log2(e) / (2 syy)) of the store below
+  __shared__ float4 s_rc[C::SPB][kKmax];
+  __shared__ float s_lw[LZ ? C::SPB : 1][LZT ? 24 : (LZ ? 12 : 1)];  // raw Lanczos weights of the stamp, per wavefront
 
   const int l = (C::SPB == 1) ? (int)threadIdx.x : (int)threadIdx.x % W;
   int slot = (C::SPB == 1) ? 0 : (int)threadIdx.x / W;
@@ -128,18 +131,8 @@ render_small_kernel(RenderArgs p) {
       }
     });
   }
-  if constexpr (LZF) {
-    // The galaxy sits at its integer position (the fractional part is the
-    // Lanczos shift), and that integer shift is applied as a Fourier phase as
-    // well (cyclic shift theorem) instead of a roll at the store: the stamp
-    // then leaves the row transform in output order, so the filter's edges
-    // are fixed at compile time.
-    G.fx = (float)G.nx;
-    G.fy = (float)G.ny;
-  }
   const float* amp = p.amp + G.table * kKmax;
   const float* var = p.var + G.table * kKmax;
-  const int kloop = C::WAVE1 ? G.K : p.kmax;
   const float trB = G.b11 + G.b22;
 
   // ---------------------------------------------------------------- column phase
@@ -316,7 +309,8 @@ render_small_kernel(RenderArgs p) {
   // the rest accumulate.
   float S[M + 1];
   float SN[2];
-  unsigned rmask = 0;  // components with a real-space share
+  unsigned rmask = 0;  // components with a real-space share: lane k holds v and (1 - w) A
+  float vk = 0.f, rak = 0.f;
   auto first_terms = [&](float v, float wa) {
     static_for<0, M + 1>([&](auto mm) {
       constexpr int m = decltype(mm)::value;
@@ -345,7 +339,7 @@ render_small_kernel(RenderArgs p) {
     // One stamp per wavefront: lane k works out the route weight of component
     // k once (K <= 16 lanes), and the loop takes v and w A from lane k.
     const int lk = (int)__lane_id();
-    float vk = 0.f, wak = 0.f;
+    float wak = 0.f;
     bool rk = false;
     if (lk < G.K) {
       vk = var[lk];
@@ -353,7 +347,7 @@ render_small_kernel(RenderArgs p) {
       const float wk = route_weight<W>(vk * trB, p.flags);
       wak = wk * Ak;
       rk = wk < 1.f && Ak != 0.f;
-      if (rk && l == lk) s_rs[slot][lk] = make_float2(vk, (1.f - wk) * Ak);
+      rak = (1.f - wk) * Ak;
     }
     rmask = (unsigned)__ballot(rk);
     FlatSum f;
@@ -374,7 +368,7 @@ render_small_kernel(RenderArgs p) {
     // Several stamps per wavefront: lane k of each stamp works out its
     // stamp's component k (K <= W lanes), and the loop takes v and w A from
     // it with a lane permute within the stamp's W lanes.
-    float vk = 0.f, wak = 0.f;
+    float wak = 0.f;
     bool rk = false;
     if (l < G.K) {
       vk = var[l];
@@ -382,14 +376,19 @@ render_small_kernel(RenderArgs p) {
       const float wk = route_weight<W>(vk * trB, p.flags);
       wak = wk * Ak;
       rk = wk < 1.f && Ak != 0.f;
-      if (rk) s_rs[slot][l] = make_float2(vk, (1.f - wk) * Ak);
+      rak = (1.f - wk) * Ak;
     }
     const unsigned long long rb = __ballot(rk);
     rmask = (unsigned)(rb >> ((int)__lane_id() & ~(W - 1))) & (unsigned)((1ull << W) - 1ull);
     FlatSum f;
     take_flat<W>(G, vk, wak, f);
     flat_terms(f);
-    for (int k = 0; k < kloop; ++k) {
+    // over the components that any of the wavefront's stamps still needs
+    unsigned long long need = __ballot(wak != 0.f);
+    need |= need >> 32;
+    if constexpr (W == 16) need |= need >> 16;
+    for (unsigned mk = (unsigned)need & ((1u << kKmax) - 1u); mk != 0; mk &= mk - 1) {
+      const int k = __builtin_ctz(mk);
       const float wa = __shfl(wak, k, W);
       if (wa == 0.f) continue;
       add_terms(__shfl(vk, k, W), wa);
@@ -402,22 +401,17 @@ render_small_kernel(RenderArgs p) {
     const float cornerv = __shfl(S[M], 1, W);  // lane 1 of the stamp: h = 1
     SN[1] = (l == W / 2) ? cornerv : mirrored;
   }
-  if constexpr (!LZF) {
-    // Lane k forms real-space component k's constants once per stamp; they
-    // do not depend on the lane's column.
-    if (l < kKmax && ((rmask >> l) & 1u)) {
-      const float2 rs = s_rs[slot][l];
-      const float v = rs.x, ra = rs.y;
-      const float sxx = fmaf(v, G.b11, pg[2]);
-      const float sxy = fmaf(v, G.b12, pg[3]);
-      const float syy = fmaf(v, G.b22, pg[4]);
-      const float det = fmaf(sxx, syy, -(sxy * sxy));
-      const float rdet = __builtin_amdgcn_rcpf(det);
-      const float rsxx = __builtin_amdgcn_rcpf(sxx);
-      s_rc[slot][l] = make_float4(__builtin_amdgcn_sqrtf(-kHalfLog2e * sxx * rdet),
-                                  ra * G.flux * pg[5] * kInv2Pi * __builtin_amdgcn_rsqf(det), -sxy * rsxx,
-                                  kHalfLog2e * rsxx);
-    }
+  // Lane k forms real-space component k's constants once per stamp; they do
+  // not depend on the row.
+  if (l < kKmax && ((rmask >> l) & 1u)) {
+    const float sxx = fmaf(vk, G.b11, pg[2]);
+    const float sxy = fmaf(vk, G.b12, pg[3]);
+    const float syy = fmaf(vk, G.b22, pg[4]);
+    const float det = fmaf(sxx, syy, -(sxy * sxy));
+    const float rsyy = __builtin_amdgcn_rcpf(syy);
+    s_rc[slot][l] = make_float4(rak * G.flux * pg[5] * kInv2Pi * __builtin_amdgcn_rsqf(det),
+                                __builtin_amdgcn_sqrtf(-kHalfLog2e * syy * __builtin_amdgcn_rcpf(det)), sxy * rsyy,
+                                kHalfLog2e * rsyy);
   }
 
   // Fractional-shift phases (shift theorem): exp(-2 pi i (fx nu + fy om)).
@@ -427,18 +421,18 @@ render_small_kernel(RenderArgs p) {
   // omega = -1/2 is the conjugate of row W/2 (omega = +1/2).
   float sy, cy;
   sincospi_poly(-2.f * G.fy * omN, &sy, &cy);
-  if constexpr (!LZF) {
-    // The integer part of the y centre goes into the phase as well:
-    // exp(-2 pi i n_y k_y / W) for row k_y = l (mod W) is an exact table
-    // entry.  The stamp then leaves the transforms in output row order, and
-    // only its columns are rolled at the store.
-    const float2 ti = twiddle_rt<-1, W>(G.ny * l);
-    const float c2 = fmaf(cy, ti.x, -(sy * ti.y)), s2 = fmaf(cy, ti.y, sy * ti.x);
-    cy = c2;
-    sy = s2;
-  }
+  // The integer parts of the centre go into the phases as well: exp(-2 pi i
+  // n_y k_y / W) for row k_y = l (mod W), and the like for k_x, are exact
+  // table entries.
+  auto with_integer = [](float& cc, float& ss, float2 ti) {
+    const float c2 = fmaf(cc, ti.x, -(ss * ti.y)), s2 = fmaf(cc, ti.y, ss * ti.x);
+    cc = c2;
+    ss = s2;
+  };
+  with_integer(cy, sy, twiddle_rt<-1, W>(G.ny * l));
   float sxa, cxa;
   sincospi_poly(h ? -G.fx : -2.f * G.fx * nu, &sxa, &cxa);
+  with_integer(cxa, sxa, twiddle_rt<-1, W>(G.nx * (h ? W / 2 : c)));
   const float sx = pair_even(sxa), cx = pair_even(cxa);
   const float sxh = stamp_lane1<W>(sxa), cxh = stamp_lane1<W>(cxa);  // nu = +1/2
   const float fs = G.flux * (1.f / ((float)W * (float)W));
@@ -527,56 +521,39 @@ render_small_kernel(RenderArgs p) {
   fft<NC, +1>(R);
 
   // ---------------------------------------------------------------- real space + store
-  // Output pixel (Y, X = l) is pixel ((Y - ny) mod W, (X - nx) mod W) of the
-  // fractional-offset Fourier image: the integer shift is a cyclic roll.  Pass
-  // q stages source rows q W/2 .. q W/2 + W/2 - 1 in LDS; they land on output
-  // rows (q W/2 + r + ny) mod W.
   float* st = reinterpret_cast<float*>(&s_t1[slot][0]);
-  const float dx = (float)l - G.x0 - pg[0];
-  const float dyc = -G.y0 - pg[1];
+  if (rmask != 0) {
+    const float dy = (float)y - G.y0 - pg[1];
+    const float dx0 = -G.x0 - pg[0];  // dx of column 0
+    for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
+      const float4 rc = s_rc[slot][__builtin_ctz(mk)];
+      // Along this lane's row (dy fixed) the quadratic form is
+      // dy^2 / syy + (syy / det) (dx - (sxy / syy) dy)^2, completed about the
+      // conditional mean, so that the exponent stays a difference of small
+      // terms near the peak (an expansion about a fixed column cancels terms
+      // of size (W/2)^2 / sxx there): with dx = x + dx0 the exponent is
+      // k - u^2, u = g (x + m), two FMAs with an immediate x.
+      const float ampr = rc.x, g = rc.y;
+      const float k0 = rc.w * dy * dy;
+      const float gm = g * fmaf(-rc.z, dy, dx0);
+      static_for<0, W / 2>([&](auto xx) {
+        constexpr int x = 2 * decltype(xx)::value;  // two columns at a time
+        const float u0 = fmaf(g, (float)x, gm);
+        const float u1 = fmaf(g, (float)(x + 1), gm);
+        R[x >> 1].x = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u0, u0, k0)), R[x >> 1].x);
+        R[x >> 1].y = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u1, u1, k0)), R[x >> 1].y);
+      });
+    }
+  }
   float* outp = p.out + (live ? stamp : 0) * (int64_t)(W * W);
   if constexpr (LZF) {
     {
       // Lanczos-3 shift by the fractional position, fused into the store: a
       // lane keeps its whole output column (W <= 64), so the stamp makes one
-      // trip to memory.  The tile is in output order (the integer shift went
-      // into the phase).  The real-space components are added to the rows
-      // first (the shift applies to the whole stamp), the rows are filtered
-      // along x in the row-owning lane and written to the LDS tile, and the
-      // columns are filtered along y in registers as the tile's rows are
-      // read.  Taps outside the stamp have weight zero.
-      if (rmask != 0) {
-        // Real-space components along this lane's row: the exponent is a
-        // quadratic in the column x with per-row coefficients, two FMAs per
-        // pixel.
-        const float dy = (float)y + dyc;
-        const float dx0 = -G.x0 - pg[0];  // dx of column 0
-        for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
-          const float2 rs = s_rs[slot][__builtin_ctz(mk)];
-          const float v = rs.x, ra = rs.y;
-          const float sxx = fmaf(v, G.b11, pg[2]);
-          const float sxy = fmaf(v, G.b12, pg[3]);
-          const float syy = fmaf(v, G.b22, pg[4]);
-          const float det = fmaf(sxx, syy, -(sxy * sxy));
-          const float rdet = __builtin_amdgcn_rcpf(det);
-          const float ampr = ra * G.flux * pg[5] * kInv2Pi * __builtin_amdgcn_rsqf(det);
-          // Along this lane's row (dy fixed) the quadratic form is
-          // dy^2 / syy + (syy / det) (dx - (sxy / syy) dy)^2, completed about
-          // the conditional mean so that no large terms cancel near the peak:
-          // with dx = x + dx0 the exponent is k - u^2, u = g (x + m).
-          const float rsyy = __builtin_amdgcn_rcpf(syy);
-          const float g = __builtin_amdgcn_sqrtf(-kHalfLog2e * syy * rdet);
-          const float k0 = kHalfLog2e * dy * dy * rsyy;
-          const float gm = g * fmaf(-sxy * rsyy, dy, dx0);
-          static_for<0, W / 2>([&](auto xx) {
-            constexpr int x = 2 * decltype(xx)::value;  // two columns at a time
-            const float u0 = fmaf(g, (float)x, gm);
-            const float u1 = fmaf(g, (float)(x + 1), gm);
-            R[x >> 1].x = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u0, u0, k0)), R[x >> 1].x);
-            R[x >> 1].y = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u1, u1, k0)), R[x >> 1].y);
-          });
-        }
-      }
+      // trip to memory.  The rows are filtered along x in the row-owning lane
+      // and written to the LDS tile, and the columns are filtered along y in
+      // registers as the tile's rows are read.  Taps outside the stamp have
+      // weight zero.
       // x filter of this lane's row, with every lane active (in the staging
       // passes below only half the lanes write, and arithmetic there would
       // be issued once per pass)
@@ -628,50 +605,19 @@ render_small_kernel(RenderArgs p) {
       }
     }
   } else {
-    const int colsrc = (l - G.nx) & (W - 1);
     float carry[5];  // LZT: rows HR - 5 .. HR - 1 of this lane's column, for the second half
+    const int c4 = 4 * (l & (W / 4 - 1)), r4 = l / (W / 4);  // this lane's four columns and first row
     static_for<0, 2>([&](auto qq) {
       constexpr int q = decltype(qq)::value;
       if (y / C::HR == q) {
-        int row = (y - q * C::HR) * (W + 1);
-        asm volatile("" : "+v"(row));  // one base address; the 2n offsets stay immediate
-        static_for<0, NC>([&](auto nn) {
+        int row = (y - q * C::HR) * C::LSO;
+        asm volatile("" : "+v"(row));  // one base address; the offsets stay immediate
+        static_for<0, W / 4>([&](auto nn) {
           constexpr int n = decltype(nn)::value;
-          st[row + 2 * n] = R[n].x;
-          st[row + 2 * n + 1] = R[n].y;
+          *reinterpret_cast<float4*>(st + row + 4 * n) = make_float4(R[2 * n].x, R[2 * n].y, R[2 * n + 1].x, R[2 * n + 1].y);
         });
       }
       __syncthreads();
-      float val[C::HR];
-      static_for<0, C::HR>([&](auto rr) {
-        constexpr int r = decltype(rr)::value;
-        val[r] = st[r * (W + 1) + colsrc];
-      });
-      if (rmask != 0) {
-        for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
-          const float4 rc = s_rc[slot][__builtin_ctz(mk)];  // LDS, not global: no wait on the stores above
-          // Along this lane's column (dx fixed) the quadratic form is
-          // dx^2 / sxx + (sxx / det) (dy - (sxy / sxx) dx)^2: the square is
-          // completed about the conditional mean, so the exponent stays a
-          // difference of small terms near the peak whatever the tile row
-          // (an expansion about the tile's first row cancels terms of size
-          // (W/2)^2 / syy there).  With dy = dyq + r the exponent is
-          // k - u^2, u = g (r + m): two FMAs with an immediate r.
-          const float g = rc.x, ampr = rc.y;
-          const float k0 = rc.w * dx * dx;
-          const float dyq = (float)(q * C::HR) + dyc;
-          const float gm = g * fmaf(rc.z, dx, dyq);
-          // two rows at a time, so that each exponential has an independent
-          // instruction between it and its use
-          static_for<0, C::HR / 2>([&](auto rr) {
-            constexpr int r = 2 * decltype(rr)::value;
-            const float u0 = fmaf(g, (float)r, gm);
-            const float u1 = fmaf(g, (float)(r + 1), gm);
-            val[r] = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u0, u0, k0)), val[r]);
-            val[r + 1] = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u1, u1, k0)), val[r + 1]);
-          });
-        }
-      }
       if constexpr (LZT) {
         // Lanczos-3 shift of the finished pixels, real-space terms included:
         // along y on the lane's column in registers (the first half's last
@@ -683,6 +629,8 @@ render_small_kernel(RenderArgs p) {
         // took 331 us (182 us that pass).
         constexpr int T0 = q == 0 ? 0 : C::HR - 2;            // output rows whose taps are in
         constexpr int NT = q == 0 ? C::HR - 2 : C::HR + 2;
+        float val[C::HR];  // this lane's column
+        static_for<0, C::HR>([&](auto rr) { val[decltype(rr)::value] = st[decltype(rr)::value * C::LSO + l]; });
         auto src = [&](auto ss) {
           constexpr int sr = decltype(ss)::value;
           if constexpr (sr < q * C::HR) return carry[sr - (C::HR - 5)];
@@ -704,9 +652,8 @@ render_small_kernel(RenderArgs p) {
         for (int i = l; i < 2 * NT; i += W)
           *reinterpret_cast<float4*>(st + (i >> 1) * LS + (i & 1) * (W + 4)) = make_float4(0.f, 0.f, 0.f, 0.f);
         __syncthreads();
-        const int c4 = 4 * (l & (W / 4 - 1));
 #pragma unroll 2
-        for (int rw = l / (W / 4); rw < NT; rw += 4) {
+        for (int rw = r4; rw < NT; rw += 4) {
           const float4* s4 = reinterpret_cast<const float4*>(st + rw * LS + c4);
           const float4 a = s4[0], b = s4[1], e = s4[2];  // columns c4 - 4 .. c4 + 7
           const float in[12] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, e.x, e.y, e.z, e.w};
@@ -720,18 +667,19 @@ render_small_kernel(RenderArgs p) {
           if (live) __builtin_nontemporal_store(o, reinterpret_cast<v4f_any*>(outp + (T0 + rw) * W + c4));
         }
       } else if (live) {
-        if (p.flags & kAccumulate) {
-          static_for<0, C::HR>([&](auto rr) {
-            constexpr int r = decltype(rr)::value;
-            float* rowp = outp + (q * C::HR + r) * W;
-            __builtin_nontemporal_store(val[r] + rowp[l], &rowp[l]);
-          });
-        } else {
-          static_for<0, C::HR>([&](auto rr) {
-            constexpr int r = decltype(rr)::value;
-            __builtin_nontemporal_store(val[r], outp + (q * C::HR + r) * W + l);  // streamed output
-          });
-        }
+        // Four pixels per lane: beside the arithmetic, four times as many
+        // 4-byte stores hold the wavefronts up (64 x 64: 491 us per 100,000
+        // stamps with them).  `out` is only promised to be aligned as floats are.
+        const bool acc = (p.flags & kAccumulate) != 0;
+        float* o = outp + (q * C::HR + r4) * W + c4;
+        static_for<0, C::HR / 4>([&](auto ii) {
+          constexpr int i = decltype(ii)::value;
+          const float4 t = *reinterpret_cast<const float4*>(st + (4 * i + r4) * C::LSO + c4);
+          v4f_any v = {t.x, t.y, t.z, t.w};
+          v4f_any* dst = reinterpret_cast<v4f_any*>(o + 4 * i * W);
+          if (acc) v += *dst;
+          __builtin_nontemporal_store(v, dst);  // streamed output
+        });
       }
       __syncthreads();
     });

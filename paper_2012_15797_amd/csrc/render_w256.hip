@@ -576,8 +576,8 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
     const bool acc = (p.flags & kAccumulate) != 0;
     static_for<0, 8>([&](auto qq) {
       constexpr int q = decltype(qq)::value;
-      v4f* dst = reinterpret_cast<v4f*>(orow + 32 * q);
-      v4f val = {zq[0][q].x, zq[0][q].y, zq[1][q].x, zq[1][q].y};
+      v4f_any* dst = reinterpret_cast<v4f_any*>(orow + 32 * q);
+      v4f_any val = {zq[0][q].x, zq[0][q].y, zq[1][q].x, zq[1][q].y};
       if (acc) val += *dst;
       __builtin_nontemporal_store(val, dst);
     });
@@ -625,14 +625,14 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
           // columns 4 lane - 3 .. 4 lane + 5
           const float e[9] = {lane_below(a[1]), lane_below(a[2]), lane_below(a[3]), a[0], a[1],
                               a[2],             a[3],             lane_above(a[0]), lane_above(a[1])};
-          v4f o;
+          v4f_any o;
           static_for<0, 4>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
             float h = 0.f;
             static_for<0, 6>([&](auto dd) { h = fmaf(wx[decltype(dd)::value], e[j + decltype(dd)::value], h); });
             o[j] = h;
           });
-          __builtin_nontemporal_store(o, reinterpret_cast<v4f*>(outp + (int64_t)(y0 + i) * W + 4 * l4));
+          __builtin_nontemporal_store(o, reinterpret_cast<v4f_any*>(outp + (int64_t)(y0 + i) * W + 4 * l4));
         });
       };
       const int y0 = half * HROWS + 8 * wv;

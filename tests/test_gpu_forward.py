@@ -311,3 +311,39 @@ def test_empty_batch_and_errors(ctx):
     with pytest.raises(gfc.GfcError):
         gfc.gfc_render_stamps(ctx, psf, mix, one, one, one, one, one, one, 64, flags=3)
     psf.close(); mix.close()
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("W", [16, 32, 64, 128, 256])
+def test_flat_components_and_stores(ctx, W, flags):
+    """The components whose exponent stays within one power of two over the
+    frequency grid, which are summed as one polynomial: tables with all, some,
+    one (not merged) and no such component, zero and negative amplitudes among
+    them, r_e from 0.02 px to W/5, hybrid and forced-Fourier routing.  Stamps of
+    one wavefront (16, 32) differ in which components are flat.  The output is
+    aligned as floats only, and a second, accumulated render doubles it."""
+    import torch
+    import paper_2012_15797_amd as gfc
+
+    rng = np.random.Generator(np.random.PCG64(1700 + W))
+    tables = [(rng.dirichlet(np.ones(16)), np.logspace(-9, -5, 16)), (rng.dirichlet(np.ones(16)), np.logspace(-4, 1, 16)),
+              (np.array([0.6, 0.4]), np.array([1e-6, 4.0])), (np.array([0.9, 0.0, -0.2, 0.3]), np.array([2e-4, 1e-3, 1e-2, 0.5])),
+              (np.array([0.5, 0.5]), np.array([3.0, 9.0]))]
+    mixtures = wl.mixture_set(tables)
+    cfg = dict(mix=mixtures, psf=wl.config_metric(4)["psf"])
+    n = 25
+    gal = wl.draw_galaxies(rng, n, W, (np.arange(n) % 5).astype(np.int32), r_e_range=(0.02, W / 5.0))
+    gal.x[:5], gal.y[:5] = [0, W - 1, W / 2, -2, W + 0.25], [W / 2, 0.5, W - 1, 3, -0.75]
+    psf, mix = lib_objects(ctx, cfg)
+    buf = torch.zeros(n * W * W + 1, device="cuda")
+    out = buf[1:].view(n, W, W)
+    args = (ctx, psf, mix, gal.x, gal.y, gal.flux, gal.r_e, gal.e1, gal.e2, W)
+    gfc.gfc_render_stamps(*args, mix_id=gal.mix_id, flags=flags, out=out)
+    once = out.clone()
+    gfc.gfc_render_stamps(*args, mix_id=gal.mix_id, flags=flags | gfc.GFC_ACCUMULATE, out=out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, 2 * once) and float(buf[0]) == 0.0
+    ref = oracle_stamps(cfg, gal, range(n), flags=flags)
+    errs = peak_errors(once.cpu().numpy().astype(np.float64), ref, range(n))
+    assert errs.max() <= TOL_PEAK, (errs.max(), int(np.argmax(errs)))
+    psf.close(); mix.close()
