@@ -326,6 +326,10 @@ __device__ __forceinline__ float vector_f(float v) {
   return r;
 }
 
+// Keeps a value's computation where it stands: the compiler otherwise sinks it
+// to a later use, with its operands (more registers) held until then.
+__device__ __forceinline__ void formed_here(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+
 // 2^x on -1 <= x <= 0 as a polynomial with value 1 at 0: the minimax fit of
 // degree 6, error 1.5e-9 (a fit in double precision, coefficients rounded).
 constexpr int kFlatDeg = 6;

@@ -185,18 +185,18 @@ render_small_kernel(RenderArgs p) {
   // PSF spectrum of this lane's bins and the PSF Gaussian (step 2; for a
   // varying PSF, the weighted sum of the components at the galaxy's image
   // position, whose transforms and moments are linear in the weights).
-  float2 Pm[M];
+  // From 64 up it is read (a varying one summed) in the PSF product itself, 8
+  // or 16 bins at a time, rather than all at once while the mixture sums are
+  // live: a constant PSF at 64 takes 116 VGPRs instead of 144, a varying one
+  // 128 instead of 160 (four wavefronts per SIMD instead of three).  Below, a
+  // varying PSF is summed before the mixture loop, while its sums are not yet
+  // live (more registers for the reads in flight).
+  constexpr bool kPsfStream = W >= 64;
+  constexpr bool kPsfFirst = EIG && !kPsfStream;
+  float2 Pm[kPsfStream ? 1 : M];
   float2 psfN;
   float pg[6];
-  // With a varying PSF (W <= 64) the components' spectra are summed before
-  // the mixture loop, while its sums are not yet live (more registers for
-  // the LDS reads in flight); otherwise the spectrum is formed after it.
-  constexpr bool kPsfFirst = EIG && W <= 64;
-  // At 64 and 128 a constant PSF's spectrum is read in the PSF product
-  // itself, 16 bins at a time, rather than all at once while the mixture
-  // sums are live: 144 -> 116 VGPRs at 64 (four wavefronts per SIMD instead
-  // of three), no spill at 128.
-  constexpr bool kPsfStream = !EIG && W >= 64;
+  float ck = 0.f;  // varying PSF, one stamp per wavefront: lane k holds component k's weight
   auto psf_terms = [&]() {
     if constexpr (EIG) {
       const int64_t g = live ? stamp : p.n - 1;
@@ -208,68 +208,23 @@ render_small_kernel(RenderArgs p) {
       }
       const float up[4] = {1.f, u, u * u, u * u * u}, vp[4] = {1.f, v, v * v, v * v * v};
       float mom[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if constexpr (!C::SHARE) {
-        static_for<0, M>([&](auto mm) { Pm[decltype(mm)::value] = make_float2(0.f, 0.f); });
-        psfN = make_float2(0.f, 0.f);
-      }
-      if constexpr (C::SHARE) {
-        // Component j (its main bins, then its Nyquist column: contiguous in
-        // the cache) is copied into one half of the workgroup's transpose
-        // buffers, which are free until the column FFT, while the four
-        // wavefronts sum component j - 1 from the other half.  Reading a half
-        // again two components later is ordered by the barrier in between.
-        constexpr int NS = M * W + W;                   // float2 per component
-        constexpr int NV = NS / 2;                      // float4 per component
-        constexpr int PER = (NV + C::BLOCK - 1) / C::BLOCK;
-        static_assert(2 * NS <= C::SPB * C::T1N, "two component spectra fit in the transpose buffers");
-        float2* buf = &s_t1[0][0];
-        const float4* src = reinterpret_cast<const float4*>(p.psf_main);
-        const int64_t sv = p.eig_stride / 2;  // float4 from one component to the next
-        // staged float4 i of this thread: index threadIdx.x + i BLOCK, clamped
-        // (the last group is partial; clamped lanes re-read and skip the store)
-        float4 st0, st1, st2, st3, st4;
-        static_assert(PER == 5, "five float4 per thread at 64 x 64");
-        const int i4 = min((int)threadIdx.x + 4 * C::BLOCK, NV - 1);
-        const bool w4 = (int)threadIdx.x + 4 * C::BLOCK < NV;
-        const float4* s0 = src + threadIdx.x;
-        st0 = s0[0]; st1 = s0[C::BLOCK]; st2 = s0[2 * C::BLOCK]; st3 = s0[3 * C::BLOCK]; st4 = src[i4];
-        // the component weights, lane k evaluating component k's polynomial
-        // (J <= 16 lanes); the loop reads them back with a lane read
+      psfN = make_float2(0.f, 0.f);
+      if constexpr (kPsfStream) {
+        // lane k evaluates component k's polynomial (J <= 16 lanes)
         static_assert(C::WAVE1, "one stamp per wavefront");
-        const float ck = (l < p.eig_J) ? eigen_weight(p, l, up, vp) : 0.f;
+        const int lk = (int)__lane_id();
+        if (lk < p.eig_J) ck = eigen_weight(p, lk, up, vp);
         for (int j = 0; j < p.eig_J; ++j) {
-          float4* dst = reinterpret_cast<float4*>(buf + (j & 1) * NS) + threadIdx.x;
-          dst[0] = st0; dst[C::BLOCK] = st1; dst[2 * C::BLOCK] = st2; dst[3 * C::BLOCK] = st3;
-          if (w4) dst[4 * C::BLOCK] = st4;
-          __syncthreads();
-          if (j + 1 < p.eig_J) {  // in flight while component j is summed
-            const float4* sj = src + (j + 1) * sv;
-            st0 = sj[threadIdx.x]; st1 = sj[threadIdx.x + C::BLOCK]; st2 = sj[threadIdx.x + 2 * C::BLOCK];
-            st3 = sj[threadIdx.x + 3 * C::BLOCK]; st4 = sj[i4];
-          }
           const float cj = lane_f(ck, j);
-          const float2* pj = buf + (j & 1) * NS;
-          if (j == 0) {  // the first component initialises the sums (eig_J >= 1)
-            static_for<0, M>([&](auto mm) {
-              constexpr int m = decltype(mm)::value;
-              Pm[m] = cscale(pj[m * W + l], cj);
-            });
-            psfN = cscale(pj[M * W + l], cj);
-          } else {
-            static_for<0, M>([&](auto mm) {
-              constexpr int m = decltype(mm)::value;
-              const float2 q = pj[m * W + l];
-              Pm[m] = make_float2(fmaf(cj, q.x, Pm[m].x), fmaf(cj, q.y, Pm[m].y));
-            });
-            const float2 qn = pj[M * W + l];
-            psfN = make_float2(fmaf(cj, qn.x, psfN.x), fmaf(cj, qn.y, psfN.y));
-          }
+          const float2 qn = p.psf_nyq[j * p.eig_stride + l];
+          psfN = make_float2(fmaf(cj, qn.x, psfN.x), fmaf(cj, qn.y, psfN.y));
           static_for<0, 6>([&](auto ii) {
             constexpr int i = decltype(ii)::value;
             mom[i] = fmaf(cj, p.eig_mom[j * 6 + i], mom[i]);
           });
         }
       } else {
+        static_for<0, M>([&](auto mm) { Pm[decltype(mm)::value] = make_float2(0.f, 0.f); });
         for (int j = 0; j < p.eig_J; ++j) {
           const float cj = eigen_weight(p, j, up, vp);
           const float2* pj = p.psf_main + j * p.eig_stride;
@@ -452,11 +407,8 @@ render_small_kernel(RenderArgs p) {
   __syncthreads();
 
   float2 Z[M];
-  static_for<0, M>([&](auto mm) {
+  auto product = [&](auto mm, float2 P) {  // Z[m] from the PSF's bin m
     constexpr int m = decltype(mm)::value;
-    float2 P;
-    if constexpr (kPsfStream) P = psfm[m * W + l];
-    else P = Pm[m];
     if constexpr (2 * m == W / 2) {
       const float2 q0 = s_py[slot][W / 2 + h];
       const float2 pyA = h ? q0 : cscale(q0, 0.5f);
@@ -465,8 +417,105 @@ render_small_kernel(RenderArgs p) {
     } else {
       Z[m] = cscale(cmul(cmul(P, s_py[slot][2 * m + h]), pxF), S[m]);
     }
-    if constexpr (kPsfStream && m % 16 == 15) __builtin_amdgcn_sched_barrier(0);  // bounds the loads in flight
-  });
+  };
+  if constexpr (EIG && C::SHARE) {
+    // Half of the bins at a time, two components at a time: their bins of the
+    // half (contiguous in the cache) are copied with 16-byte loads into one
+    // half of the workgroup's transpose buffers, which are free until the
+    // column FFT, while the four wavefronts sum the two before from the other
+    // half.  Reading a half again two steps later is ordered by the barrier in
+    // between.  (A component past the last is the last, with weight zero.)
+    // 30,000 stamps, 6 components: 196 us, against 213 us with the whole
+    // spectrum summed before the mixture loop, at three wavefronts per SIMD.
+    constexpr int HB = M / 2;                // bins of a half
+    constexpr int NB = HB * W;               // float2 of one component's half
+    static_assert(NB / 2 == 2 * C::BLOCK && 4 * NB <= C::SPB * T1N, "two float4 per thread and component; the buffers fit");
+    float2* buf = &s_t1[0][0];
+    const float4* src = reinterpret_cast<const float4*>(p.psf_main) + threadIdx.x;
+    const int64_t sv = p.eig_stride / 2;     // float4 from one component to the next
+    const int np = (p.eig_J + 1) >> 1, last = p.eig_J - 1;
+    float4 st0, st1, st2, st3;
+    auto fetch = [&](int half, int jp) {     // components 2 jp, 2 jp + 1
+      const float4* a = src + half * (NB / 2);
+      const float4* b = a + min(2 * jp + 1, last) * sv;
+      a += 2 * jp * sv;
+      st0 = a[0], st1 = a[C::BLOCK], st2 = b[0], st3 = b[C::BLOCK];
+    };
+    fetch(0, 0);
+    int it = 0;
+    static_for<0, 2>([&](auto hh) {
+      constexpr int half = decltype(hh)::value;
+      float2 P[HB];  // (started at zero: the first pair apart takes 136 registers)
+      static_for<0, HB>([&](auto ii) { P[decltype(ii)::value] = make_float2(0.f, 0.f); });
+      for (int jp = 0; jp < np; ++jp, ++it) {
+        float2* b = buf + (it & 1) * (2 * NB);
+        float4* dst = reinterpret_cast<float4*>(b) + threadIdx.x;
+        dst[0] = st0, dst[C::BLOCK] = st1, dst[NB / 2] = st2, dst[NB / 2 + C::BLOCK] = st3;
+        __syncthreads();
+        if (jp + 1 < np) fetch(half, jp + 1);  // in flight while these are summed
+        else if constexpr (half == 0) fetch(1, 0);
+        const float c0 = vector_f(lane_f(ck, 2 * jp)), c1 = vector_f(lane_f(ck, 2 * jp + 1));  // lanes past J hold zero
+        static_for<0, HB>([&](auto ii) {
+          constexpr int i = decltype(ii)::value;
+          const float2 q0 = b[i * W + l], q1 = b[NB + i * W + l];
+          P[i] = make_float2(fmaf(c1, q1.x, fmaf(c0, q0.x, P[i].x)), fmaf(c1, q1.y, fmaf(c0, q0.y, P[i].y)));
+        });
+      }
+      static_for<0, HB>([&](auto ii) {
+        constexpr int m = half * HB + decltype(ii)::value;
+        product(std::integral_constant<int, m>{}, P[decltype(ii)::value]);
+        formed_here(Z[m]);
+      });
+    });
+    __syncthreads();  // the buffers take the transpose
+  } else if constexpr (EIG && kPsfStream) {
+    // Eight bins at a time; each component's eight are in flight while the
+    // one before is summed, two components per trip.  (A component past the
+    // last is the last, with weight zero.)  5,000 stamps of 128 x 128, 6
+    // components: 209 us, against 305 us with all bins of one component read
+    // at a time after the mixture loop, which spilled.
+    const float2* pj = p.psf_main + l;
+    const int last = p.eig_J - 1;
+    float2 qa[8], qb[8];
+    auto fetch = [&](float2 (&q)[8], auto gg, int j) {
+      static_for<0, 8>([&](auto ii) {
+        constexpr int i = decltype(ii)::value;
+        q[i] = pj[j * p.eig_stride + (8 * decltype(gg)::value + i) * W];
+      });
+    };
+    fetch(qa, std::integral_constant<int, 0>{}, 0);
+    static_for<0, M / 8>([&](auto gg) {
+      constexpr int g = decltype(gg)::value;
+      float2 P[8];
+      static_for<0, 8>([&](auto ii) { P[decltype(ii)::value] = make_float2(0.f, 0.f); });
+      auto sum = [&](const float2 (&q)[8], int j) {
+        const float cj = vector_f(lane_f(ck, j));  // lanes past J hold zero
+        static_for<0, 8>([&](auto ii) {
+          constexpr int i = decltype(ii)::value;
+          P[i] = make_float2(fmaf(cj, q[i].x, P[i].x), fmaf(cj, q[i].y, P[i].y));
+        });
+      };
+      for (int j = 0; j <= last; j += 2) {
+        fetch(qb, gg, min(j + 1, last));
+        sum(qa, j);
+        if (j + 2 <= last) fetch(qa, gg, j + 2);
+        else if constexpr (g + 1 < M / 8) fetch(qa, std::integral_constant<int, g + 1>{}, 0);
+        sum(qb, j + 1);
+      }
+      static_for<0, 8>([&](auto ii) {
+        constexpr int m = 8 * g + decltype(ii)::value;
+        product(std::integral_constant<int, m>{}, P[decltype(ii)::value]);
+        formed_here(Z[m]);
+      });
+    });
+  } else {
+    static_for<0, M>([&](auto mm) {
+      constexpr int m = decltype(mm)::value;
+      if constexpr (kPsfStream) product(mm, psfm[m * W + l]);
+      else product(mm, Pm[m]);
+      if constexpr (kPsfStream && m % 16 == 15) __builtin_amdgcn_sched_barrier(0);  // bounds the loads in flight
+    });
+  }
   if (c == 0) {  // column 0 carries the Nyquist column as its imaginary part
     static_for<0, M>([&](auto mm) {
       constexpr int m = decltype(mm)::value;

@@ -207,7 +207,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
     const float u = uniform_f((__builtin_bit_cast(float, in[8]) - p.eig_norm[0]) * p.eig_norm[1]);
     const float v = uniform_f((__builtin_bit_cast(float, in[9]) - p.eig_norm[2]) * p.eig_norm[3]);
     const float up[4] = {1.f, u, u * u, u * u * u}, vp[4] = {1.f, v, v * v, v * v * v};
-    if (t < p.eig_J) s_cj[t] = eigen_weight(p, t, up, vp);
+    if (t < kEigMax) s_cj[t] = t < p.eig_J ? eigen_weight(p, t, up, vp) : 0.f;
     __syncthreads();
     float mom[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int j = 0; j < p.eig_J; ++j) {
@@ -391,20 +391,38 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
   // time (for a varying PSF the component loop runs inside each group).
   float2 Z[M];
   const int pidx0 = (h >> 2) * (4 * NC) + 4 * c + (h & 3);
+  // EIG: a component's bins of a group are in flight while the one before is
+  // summed, two components per trip (past the last: the last, with weight
+  // zero).  1,000 stamps, 6 components: 196 us, against 320 us with each
+  // component's eight waited for in turn.
+  float2 qa[EIG ? 8 : 1], qb[EIG ? 8 : 1];
+  const int last = p.eig_J - 1;
+  auto fetch = [&](float2 (&q)[EIG ? 8 : 1], auto gg, int j) {
+    const GlobalF2 src = (GlobalF2)(p.psf_main + (int64_t)j * p.eig_stride);
+    static_for<0, 8>([&](auto ii) {
+      constexpr int i = decltype(ii)::value;
+      q[i] = ld2(src, pidx0 + 2 * (8 * decltype(gg)::value + i) * (4 * NC));
+    });
+  };
+  if constexpr (EIG) fetch(qa, std::integral_constant<int, 0>{}, 0);
   static_for<0, M / 8>([&](auto gg) {
     constexpr int g = decltype(gg)::value;
     float2 P[8];
     if constexpr (EIG) {
       static_for<0, 8>([&](auto ii) { P[decltype(ii)::value] = make_float2(0.f, 0.f); });
-#pragma unroll 1
-      for (int j = 0; j < p.eig_J; ++j) {
+      auto sum = [&](const float2 (&q)[8], int j) {
         const float cj = s_cj[j];
-        const float2* q = p.psf_main + (int64_t)j * p.eig_stride + pidx0;
         static_for<0, 8>([&](auto ii) {
           constexpr int i = decltype(ii)::value;
-          const float2 v = q[2 * (8 * g + i) * (4 * NC)];
-          P[i] = make_float2(fmaf(cj, v.x, P[i].x), fmaf(cj, v.y, P[i].y));
+          P[i] = make_float2(fmaf(cj, q[i].x, P[i].x), fmaf(cj, q[i].y, P[i].y));
         });
+      };
+      for (int j = 0; j <= last; j += 2) {
+        fetch(qb, gg, min(j + 1, last));
+        sum(qa, j);
+        if (j + 2 <= last) fetch(qa, gg, j + 2);
+        else if constexpr (g + 1 < M / 8) fetch(qa, std::integral_constant<int, g + 1>{}, 0);
+        sum(qb, j + 1);
       }
     }
     static_for<0, 8>([&](auto ii) {
@@ -419,6 +437,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
       } else {
         Z[m] = cscale(cmul(cmul(P[i], s_py[D * m + h]), pxF), S[m]);
       }
+      if constexpr (EIG) formed_here(Z[m]);
     });
     __builtin_amdgcn_sched_barrier(0);  // bounds the PSF loads in flight
   });

@@ -119,6 +119,31 @@ def test_single_component_matches_constant_psf(ctx):
     a.close(); b.close(); mix.close()
 
 
+@pytest.mark.parametrize("J", [1, 2, 3, 15, 16])
+@pytest.mark.parametrize("W", [32, 64, 128, 256])
+def test_eigen_component_counts(ctx, eig, W, J):
+    """Odd and even component counts up to the largest (the components are
+    summed two at a time, the one past the last with weight zero), five stamps
+    (a partial workgroup of four at 64): the first components carry the PSF,
+    the rest small multiples of its parts."""
+    rng = np.random.Generator(np.random.PCG64(880 + J))
+    base = np.asarray(eig["comps"], np.float32)
+    comps = np.stack([base[0] if j == 0 else base[j % 6] * np.float32(0.3 if j < 6 else 0.01 * j) for j in range(J)])
+    coef = np.zeros((J, 6))
+    coef[0, 0] = 1.0
+    coef[1:] = rng.normal(0.0, 0.2, (J - 1, 6))
+    e = dict(comps=comps, coef=coef, degree=2, norm=eig["norm"])
+    cfg = wl.config_metric(10)
+    n = 5
+    gal = wl.draw_galaxies(rng, n, W, 0, r_e_range=(0.5, W / 6.0))
+    px, py = (rng.uniform(0, 4096, n).astype(np.float32) for _ in range(2))
+    psf, mix = _lib(ctx, e, cfg["mix"])
+    gpu = _render(ctx, psf, mix, gal, W, px, py)
+    ref = oe.render_batch_eigen(_eig64(e), cfg["mix"].as_f32(), gal, px, py, idx=range(n))
+    _check(gpu, ref, range(n))
+    psf.close(); mix.close()
+
+
 def test_full_size_eigen_workload_sampled(ctx):
     """The 100,000-stamp eigen-PSF workload in one launch, sampled."""
     cfg = wl.config_eigen()
