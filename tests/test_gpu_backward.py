@@ -313,3 +313,46 @@ def test_amplitude_sums_across_chunks_and_tables(ctx, n_tables):
     first = _PER_GALAXY.setdefault("per_gal", per_gal)
     assert np.array_equal(per_gal, first)
     psf.close(); mix.close()
+
+
+@pytest.mark.parametrize("n,n_tables", [(1, 1), (64, 16), (65, 2), (2048, 3), (2049, 3), (2048, 17)])
+def test_amplitude_sums_in_one_launch(ctx, n, n_tables):
+    """The amplitude sums on both sides of the one-launch reduction's limits
+    (2,048 galaxies, 16 tables) and at its row remainders, added to what
+    grad_amp held.  Each galaxy's contribution is taken from a call with one
+    galaxy per table.  A sum of at most 2,049 terms passes through at most 33
+    additions in a thread and 10 after it, each rounding by 2^-24 of the sum
+    of the terms' sizes."""
+    import torch
+    import paper_2012_15797_amd as gfc
+
+    W = 16
+    rng = np.random.Generator(np.random.PCG64(710 + n + n_tables))
+    cfg = wl.config_metric(10)
+    m = cfg["mix"].as_f32()
+
+    def tables(t):
+        return gfc.Mixture(ctx, np.full(t, int(m.K[0]), np.int32),
+                           np.broadcast_to(np.asarray(m.amp, np.float32)[:1], (t, 16)),
+                           np.broadcast_to(np.asarray(m.var, np.float32)[:1], (t, 16)))
+
+    psf = gfc.Psf(ctx, cfg["psf"], cfg.get("psf_gauss"))
+    gal = wl.draw_galaxies(rng, n, W, 0)
+    g = torch.as_tensor(rng.standard_normal((n, W, W)).astype(np.float32)).cuda()
+
+    def amp_sums(mix, mix_id, into=None):
+        _, ga = gfc.gfc_render_stamps_backward(ctx, psf, mix, gal.x, gal.y, gal.flux, gal.r_e, gal.e1, gal.e2, W, g,
+                                               mix_id=np.asarray(mix_id, np.int32), grad_amp=into)
+        torch.cuda.synchronize()
+        return ga.cpu().numpy().astype(np.float64)
+
+    own, mix = tables(max(n, 17)), tables(n_tables)
+    per_gal = amp_sums(own, np.arange(n))[:n]
+    mid = rng.integers(0, n_tables, n)
+    held = rng.standard_normal((n_tables, 16)).astype(np.float32)
+    got = amp_sums(mix, mid, torch.as_tensor(held).cuda())
+    ref, scale = held.astype(np.float64), np.abs(held).astype(np.float64)
+    np.add.at(ref, mid, per_gal)
+    np.add.at(scale, mid, np.abs(per_gal))
+    assert (np.abs(got - ref) <= 44 * 2.0 ** -24 * scale).all()
+    psf.close(); own.close(); mix.close()
