@@ -21,7 +21,7 @@
 //                 negligible blocks skipped as in the 256 x 256 forward.
 //  sums           fixed-order reductions, then the chain rule on the first
 //                 wavefront.
-// The integer centre enters the phases as exact table entries, so g is never
+// The integer centre enters the phases (shift_phase), so g is never
 // rolled.
 //
 // What bounds it is VALU issue (about 4,500 instructions per wavefront and
@@ -231,8 +231,8 @@ render_bwd_split_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
   float2 cA, cB;
   {
     float sx, cx;
-    sincospi_poly(-2.f * G.fx * nu, &sx, &cx);
-    const float2 px = cscale(cmul(make_float2(cx, sx), twiddle_rt<-1, W>(G.nx * c)), 1.f / ((float)W * (float)W));
+    shift_phase<W>(G.fx, G.nx, c, &sx, &cx);
+    const float2 px = cscale(make_float2(cx, sx), 1.f / ((float)W * (float)W));
     const float2 tw = rot90<-1>(twiddle_rt<-1, W>(c));
     cA = cmulc(make_float2(1.f + tw.x, tw.y), px);
     cB = cmulc(make_float2(1.f - tw.x, -tw.y), px);
@@ -348,8 +348,8 @@ render_bwd_split_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
   float2 py = make_float2(1.f, 0.f);
   if (nyq) {
     float sy, cy;
-    sincospi_poly(-2.f * G.fy * omN, &sy, &cy);
-    py = cmul(make_float2(cy, sy), twiddle_rt<-1, W>(G.ny * t));
+    shift_phase<W>(G.fy, G.ny, t <= W / 2 ? t : t - W, &sy, &cy);
+    py = make_float2(cy, sy);
     s_py[t] = py;
     if (t == W / 2) s_py[W] = cconj(py);  // omega = -1/2 (the integer part's phase is real there)
   }

@@ -19,8 +19,8 @@
 //  store         real-space components (step 8) are added to the row in its
 //                lane's registers, and half a stamp at a time goes through LDS
 //                to memory, four pixels per lane.
-// The integer parts of the centre enter the phases as exact table entries, so
-// the stamp leaves the transforms in output order.
+// The phases are those of the whole shift, integer parts included, so the
+// stamp leaves the transforms in output order.
 #include "gfc_device.hpp"
 #include "gfc_launch.hpp"
 
@@ -374,20 +374,10 @@ render_small_kernel(RenderArgs p) {
   // that of column c, lanes h = 1 that of nu = +1/2 (the Nyquist column).
   // The h = 1 lane of a pair takes its column's phase from its neighbour;
   // omega = -1/2 is the conjugate of row W/2 (omega = +1/2).
-  float sy, cy;
-  sincospi_poly(-2.f * G.fy * omN, &sy, &cy);
-  // The integer parts of the centre go into the phases as well: exp(-2 pi i
-  // n_y k_y / W) for row k_y = l (mod W), and the like for k_x, are exact
-  // table entries.
-  auto with_integer = [](float& cc, float& ss, float2 ti) {
-    const float c2 = fmaf(cc, ti.x, -(ss * ti.y)), s2 = fmaf(cc, ti.y, ss * ti.x);
-    cc = c2;
-    ss = s2;
-  };
-  with_integer(cy, sy, twiddle_rt<-1, W>(G.ny * l));
-  float sxa, cxa;
-  sincospi_poly(h ? -G.fx : -2.f * G.fx * nu, &sxa, &cxa);
-  with_integer(cxa, sxa, twiddle_rt<-1, W>(G.nx * (h ? W / 2 : c)));
+  // The integer parts of the centre go into the phases as well.
+  float sy, cy, sxa, cxa;
+  shift_phase<W>(G.fy, G.ny, l <= W / 2 ? l : l - W, &sy, &cy);
+  shift_phase<W>(G.fx, G.nx, h ? W / 2 : c, &sxa, &cxa);
   const float sx = pair_even(sxa), cx = pair_even(cxa);
   const float sxh = stamp_lane1<W>(sxa), cxh = stamp_lane1<W>(cxa);  // nu = +1/2
   const float fs = G.flux * (1.f / ((float)W * (float)W));
