@@ -189,7 +189,7 @@ typedef struct {
                             this call instead of the mixture's (its component counts
                             and variances still apply), or NULL; the mixture itself
                             is not changed.  Not used by the Sersic and composite
-                            renders, which build their own tables. */
+                            renders. */
 } gfc_galaxies;
 
 /* Steps 3-8 for n galaxies into stamps of size W, asynchronously on
@@ -199,8 +199,8 @@ typedef struct {
  * PSF-FT cache fill of the first call for a PSF and W (gfc_psf_prepare
  * makes it beforehand), no device memory is allocated inside the call at
  * any W: the half spectrum stays on the chip (at W = 256 one workgroup per
- * CU renders a stamp at a time).  The Sersic and composite renders below
- * allocate their per-galaxy tables. */
+ * CU renders a stamp at a time).  The same holds for the Sersic and composite
+ * renders below. */
 gfc_status gfc_render_stamps(gfc_ctx* ctx, gfc_psf* psf, const gfc_mix* mix,
                              const gfc_galaxies* gal, int64_t n, int W, unsigned flags,
                              float* out, void* hip_stream);
@@ -220,7 +220,7 @@ gfc_status gfc_sersic_destroy(gfc_sersic* fam);
  * sersic_n[i] (device float32 [n]), per component for amplitudes and
  * variances.  sersic_n outside [n_grid[0], n_grid[S-1]] or not finite gives an
  * invalid galaxy (NaN stamp, counted).  gal->mix_id must be NULL.  Otherwise
- * as gfc_render_stamps; stream-ordered scratch of 136 bytes per galaxy. */
+ * as gfc_render_stamps. */
 gfc_status gfc_render_stamps_sersic(gfc_ctx* ctx, gfc_psf* psf, const gfc_sersic* fam,
                                     const gfc_galaxies* gal, const float* sersic_n, int64_t n, int W,
                                     unsigned flags, float* out, void* hip_stream);

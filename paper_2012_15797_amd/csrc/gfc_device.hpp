@@ -56,7 +56,18 @@ struct RenderArgs {
   const float2* const* psf_nyq_tab;   // [n_psf] Nyquist columns
   const float* pg_tab;                // [n_psf][6] PSF Gaussians
   int n_psf;
+  // Galaxies with a mixture of their own (forward render only; mix_id, K and
+  // n_tables are then unused): see component_mix.
+  int prof;                 // kProfTable, kProfSersic or kProfComposite
+  const float* prof_a;      // [n] Sersic index | bulge fraction
+  const float* prof_b;      // [n]              | bulge radius ratio
+  const float* prof_grid;   // [S] Sersic indices; amp and var are then [S][k1]
+  int prof_S;
+  int prof_k1, prof_k2;     // components (Sersic: k1; composite: disk, bulge)
+  int prof_disk, prof_bulge;  // the composite's tables
 };
+
+enum : int { kProfTable = 0, kProfSersic = 1, kProfComposite = 2 };
 
 constexpr int kEigMax = 16;     // eigen-PSF components
 constexpr int kEigDegMax = 3;   // polynomial degree
@@ -91,7 +102,8 @@ __device__ __forceinline__ GalaxyIn load_galaxy_in(const RenderArgs& p, int64_t 
   return GalaxyIn{p.x[g], p.y[g], p.flux[g], p.r_e[g], p.e1[g], p.e2[g], p.mix_id ? p.mix_id[g] : 0};
 }
 
-template <int W>
+// PROF: the launch may have mixtures of the galaxies' own (p.prof).
+template <int W, bool PROF = false>
 __device__ __forceinline__ Galaxy make_galaxy(const RenderArgs& p, const GalaxyIn& in) {
   Galaxy G;
   G.x0 = in.x;
@@ -101,9 +113,10 @@ __device__ __forceinline__ Galaxy make_galaxy(const RenderArgs& p, const GalaxyI
   // The table follows from mix_id alone (an index out of range takes table
   // 0 and makes the galaxy invalid), so its reads need not wait for the
   // other parameters.
-  const bool table_ok = in.table >= 0 && in.table < p.n_tables;
-  G.table = table_ok ? in.table : 0;
-  G.K = p.K[G.table];
+  const bool own = PROF && p.prof != kProfTable;
+  const bool table_ok = own || (in.table >= 0 && in.table < p.n_tables);
+  G.table = !own && table_ok ? in.table : 0;
+  G.K = own ? p.prof_k1 + p.prof_k2 : p.K[G.table];
   const float esq = e1 * e1 + e2 * e2;
   G.ok = finitef(G.x0) && finitef(G.y0) && finitef(G.flux) && finitef(re) && finitef(e1) &&
          finitef(e2) && re > 0.f && esq < 1.f && fabsf(G.x0) <= 8388608.f &&
@@ -138,9 +151,55 @@ __device__ __forceinline__ Galaxy make_galaxy(const RenderArgs& p, const GalaxyI
   return G;
 }
 
-template <int W>
+template <int W, bool PROF = false>
 __device__ __forceinline__ Galaxy load_galaxy(const RenderArgs& p, int64_t g) {
-  return make_galaxy<W>(p, load_galaxy_in(p, g));
+  return make_galaxy<W, PROF>(p, load_galaxy_in(p, g));
+}
+
+// A galaxy's own mixture (p.prof): its place in the Sersic grid, cell s and
+// fraction t, or the composite's bulge fraction t and radius ratio r.
+struct Profile {
+  float t, r;
+  int s;
+  bool ok;
+};
+
+// From the galaxy's prof_a and prof_b values, by the LANES consecutive lanes
+// that hold them (a power of two; every lane of the wavefront takes part): a
+// lane compares one grid index, so the search is one load deep for any grid
+// of up to LANES + 2 indices.
+template <int LANES>
+__device__ __forceinline__ Profile make_profile(const RenderArgs& p, float a, float b) {
+  if (p.prof == kProfComposite)
+    return Profile{a, b, 0, a >= 0.f && a <= 1.f && b > 0.f && __builtin_isfinite(b)};
+  const float* grid = p.prof_grid;
+  const int S = p.prof_S, lane = (int)__lane_id();
+  int s = 0;  // the last cell that starts at or below a; 0 if none
+  for (int i0 = 1; i0 < S - 1; i0 += LANES) {
+    const int i = i0 + (lane & (LANES - 1));
+    unsigned long long le = __ballot(i < S - 1 && grid[min(i, S - 1)] <= a);
+    if constexpr (LANES < 64) le = (le >> (lane & ~(LANES - 1))) & ((1ull << LANES) - 1ull);
+    s += __popcll(le);
+  }
+  const bool ok = __builtin_isfinite(a) && a >= grid[0] && a <= grid[S - 1];
+  const float t = ok ? (a - grid[s]) / (grid[s + 1] - grid[s]) : 0.f;
+  return Profile{t, 1.f, s, ok};
+}
+
+// Amplitude and variance of component k < G.K.  Sersic: interpolated between
+// the cell's two grid indices.  Composite: the disk's components with
+// amplitudes (1 - t) A_d, then the bulge's with t A_b and variances r^2 v_b.
+__device__ __forceinline__ float2 component_mix(const RenderArgs& p, const Galaxy& G, const Profile& f, int k) {
+  if (p.prof == kProfTable) return make_float2(p.amp[G.table * kKmax + k], p.var[G.table * kKmax + k]);
+  const float t0 = 1.f - f.t;
+  if (p.prof == kProfSersic) {
+    const int K = p.prof_k1, i = f.s * K + k;
+    return make_float2(fmaf(t0, p.amp[i], f.t * p.amp[i + K]), fmaf(t0, p.var[i], f.t * p.var[i + K]));
+  }
+  const bool disk = k < p.prof_k1;
+  const int i = disk ? p.prof_disk * kKmax + k : p.prof_bulge * kKmax + (k - p.prof_k1);
+  const float A = p.amp[i], v = p.var[i];
+  return disk ? make_float2(t0 * A, v) : make_float2(f.t * A, (f.r * f.r) * v);
 }
 
 // Fourier bins where a component's exponent (log2 of its share of the

@@ -79,7 +79,16 @@ render_small_kernel(RenderArgs p) {
   if constexpr (C::WAVE1 && C::SPB > 1) slot = __builtin_amdgcn_readfirstlane(slot);  // keeps the stamp index scalar
   const int64_t stamp = (int64_t)blockIdx.x * C::SPB + slot;
   const bool live = stamp < p.n;
-  Galaxy G = load_galaxy<W>(p, live ? stamp : p.n - 1);
+  Galaxy G = load_galaxy<W, true>(p, live ? stamp : p.n - 1);
+  Profile prof = {0.f, 0.f, 0, true};
+  if (p.prof != kProfTable) {
+    const int64_t gs = live ? stamp : p.n - 1;
+    prof = make_profile<(W < 64 ? W : 64)>(p, p.prof_a[gs], p.prof_b ? p.prof_b[gs] : 0.f);
+    if (!prof.ok) {  // invalid galaxy: NaN stamp, counted
+      G.ok = false;
+      G.flux = __builtin_nanf("");
+    }
+  }
   if constexpr (C::WAVE1) {  // one stamp per wavefront: keep its integer shift in SGPRs
     make_uniform(G);
   }
@@ -131,8 +140,6 @@ render_small_kernel(RenderArgs p) {
       }
     });
   }
-  const float* amp = p.amp + G.table * kKmax;
-  const float* var = p.var + G.table * kKmax;
   const float trB = G.b11 + G.b22;
 
   // ---------------------------------------------------------------- column phase
@@ -297,8 +304,9 @@ render_small_kernel(RenderArgs p) {
     float wak = 0.f;
     bool rk = false;
     if (lk < G.K) {
-      vk = var[lk];
-      const float Ak = amp[lk];
+      const float2 av = component_mix(p, G, prof, lk);
+      const float Ak = av.x;
+      vk = av.y;
       const float wk = route_weight<W>(vk * trB, p.flags);
       wak = wk * Ak;
       rk = wk < 1.f && Ak != 0.f;
@@ -326,8 +334,9 @@ render_small_kernel(RenderArgs p) {
     float wak = 0.f;
     bool rk = false;
     if (l < G.K) {
-      vk = var[l];
-      const float Ak = amp[l];
+      const float2 av = component_mix(p, G, prof, l);
+      const float Ak = av.x;
+      vk = av.y;
       const float wk = route_weight<W>(vk * trB, p.flags);
       wak = wk * Ak;
       rk = wk < 1.f && Ak != 0.f;
@@ -745,6 +754,8 @@ static hipError_t launch_small(const RenderArgs& args, hipStream_t stream) {
     p.psf_px = args.psf_px ? args.psf_px + done : nullptr;
     p.psf_py = args.psf_py ? args.psf_py + done : nullptr;
     p.psf_id = args.psf_id ? args.psf_id + done : nullptr;
+    p.prof_a = args.prof_a ? args.prof_a + done : nullptr;
+    p.prof_b = args.prof_b ? args.prof_b + done : nullptr;
     p.n = chunk;
     const unsigned blocks = (unsigned)((chunk + C::SPB - 1) / C::SPB);
     hipLaunchKernelGGL((render_small_kernel<W, EIG, LZ, PT>), dim3(blocks), dim3(C::BLOCK), 0, stream, p);

@@ -33,7 +33,7 @@ namespace gfc {
 
 // Inputs of stamp g that the kernel reads per stamp, as 32-bit words:
 // x, y, flux, r_e, e1, e2, mixture id, PSF id (PT), PSF position (EIG).
-constexpr int kInWords = 10;
+constexpr int kInWords = 12;
 
 template <bool EIG, bool PT>
 __device__ __forceinline__ uint32_t stamp_word(const RenderArgs& p, int64_t g, int i) {
@@ -47,9 +47,11 @@ __device__ __forceinline__ uint32_t stamp_word(const RenderArgs& p, int64_t g, i
     f = i == 8 ? p.psf_px : f;
     f = i == 9 ? p.psf_py : f;
   }
+  f = i == 10 ? p.prof_a : f;
+  f = i == 11 ? p.prof_b : f;
   const int* n = i == 6 ? p.mix_id : nullptr;
   if constexpr (PT) n = i == 7 ? p.psf_id : n;
-  const bool word_of_f = i < 6 || (EIG && i >= 8);
+  const bool word_of_f = i < 6 || (EIG && (i == 8 || i == 9)) || (i >= 10 && f);
   if (word_of_f) return __builtin_bit_cast(uint32_t, f[g]);
   return n ? (uint32_t)n[g] : 0u;
 }
@@ -63,16 +65,24 @@ constexpr int kGalWords = 16;
 // along x, then along y, in s_lw[12].
 template <int W, bool LZ>
 __device__ __forceinline__ void publish_galaxy(const RenderArgs& p, uint32_t word, int lane, uint32_t* s_gal,
-                                               float* s_lw) {
+                                               float2* s_mix, float* s_lw) {
   uint32_t w[7];
   static_for<0, 7>([&](auto ii) {
     constexpr int i = decltype(ii)::value;
     w[i] = (uint32_t)__builtin_amdgcn_readlane((int)word, i);
   });
-  const Galaxy G = make_galaxy<W>(p, GalaxyIn{__builtin_bit_cast(float, w[0]), __builtin_bit_cast(float, w[1]),
+  Galaxy G = make_galaxy<W, true>(p, GalaxyIn{__builtin_bit_cast(float, w[0]), __builtin_bit_cast(float, w[1]),
                                               __builtin_bit_cast(float, w[2]), __builtin_bit_cast(float, w[3]),
                                               __builtin_bit_cast(float, w[4]), __builtin_bit_cast(float, w[5]),
                                               (int)w[6]});
+  Profile prof = {0.f, 0.f, 0, true};
+  if (p.prof != kProfTable) {
+    prof = make_profile<64>(p, lane_f(__builtin_bit_cast(float, word), 10), lane_f(__builtin_bit_cast(float, word), 11));
+    if (!prof.ok) {  // invalid galaxy: NaN stamp, counted
+      G.ok = false;
+      G.flux = __builtin_nanf("");
+    }
+  }
   if constexpr (LZ) {
     const float v = __builtin_bit_cast(float, lane < 6 ? w[0] : w[1]);
     const float raw = lane < 12 ? lanczos3((float)((lane % 6) - 3) + (v - floorf(v))) : 0.f;
@@ -94,6 +104,7 @@ __device__ __forceinline__ void publish_galaxy(const RenderArgs& p, uint32_t wor
                       (uint32_t)G.K);
     d[3] = make_uint4(G.ok ? 1u : 0u, __builtin_bit_cast(uint32_t, lamq), 0u, 0u);
   }
+  if (lane < G.K) s_mix[lane] = component_mix(p, G, prof, lane);
 }
 
 // The published galaxy, in scalar registers.
@@ -148,11 +159,12 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
   __shared__ float s_cj[kEigMax];   // eigen-PSF component weights at this galaxy's position
   __shared__ uint32_t s_in[kInWords];
   __shared__ __attribute__((aligned(16))) uint32_t s_gal[kGalWords];
+  __shared__ float2 s_mix[kKmax];   // amplitude and variance per component of the galaxy
 
   {
     const uint32_t w0 = threadIdx.x < kInWords ? stamp_word<EIG, PT>(pa, blockIdx.x, threadIdx.x) : 0u;
     if (threadIdx.x < kInWords) s_in[threadIdx.x] = w0;
-    if (threadIdx.x < 64) publish_galaxy<W, LZ>(pa, w0, (int)threadIdx.x, s_gal, s_lw);
+    if (threadIdx.x < 64) publish_galaxy<W, LZ>(pa, w0, (int)threadIdx.x, s_gal, s_mix, s_lw);
   }
   if (threadIdx.x < 256) {
     const int hh = threadIdx.x >> 5, kg = threadIdx.x & 31;  // kg = 8 k + g
@@ -293,8 +305,9 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
   {
     const int lk = lane;
     if (lk < G.K) {
-      vk = p.var[G.table * kKmax + lk];
-      const float Ak = p.amp[G.table * kKmax + lk];
+      const float2 av = s_mix[lk];
+      const float Ak = av.x;
+      vk = av.y;
       const float wk = route_weight<W>(vk * trB, p.flags);
       wak = wk * Ak;
       rk = wk < 1.f && Ak != 0.f;
@@ -661,10 +674,10 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
     }
   });
   if (!G.ok && t == 0) atomicAdd(p.invalid, 1ull);
-  // every thread read s_in and s_gal at this stamp's start, before the
+  // every thread read s_in, s_gal and s_mix at this stamp's start, before the
   // barriers above
   if (t < kInWords) s_in[t] = in_next;
-  if (wv == 0) publish_galaxy<W, LZ>(p, in_next, lane, s_gal, s_lw);
+  if (wv == 0) publish_galaxy<W, LZ>(p, in_next, lane, s_gal, s_mix, s_lw);
   }  // stamps of this workgroup
 }
 

@@ -220,3 +220,38 @@ def test_sersic_with_eigen_psf_and_lanczos(ctx):
                                            p["flux"], p["r_e"], p["e1"], p["e2"], 64))
     _check(gpu, ref, list(range(n)))
     psf.close(); f.close()
+
+
+@pytest.mark.parametrize("S", [2, 3, 18, 66, 256])
+@pytest.mark.parametrize("W", [16, 64, 128, 256])
+def test_sersic_grid_search(ctx, W, S):
+    """Grids of two to 256 indices (one index per lane and as many rounds as
+    the stamp's lanes need), with unrelated mixtures at neighbouring indices:
+    galaxies on the indices, one float below them, at both ends and just
+    outside, against the render with the same mixtures given as one table per
+    galaxy (interpolated here in float64).  An index taken wrongly changes the
+    stamp by order one; the two interpolations differ by float32 rounding."""
+    import paper_2012_15797_amd as gfc
+    rng = np.random.Generator(np.random.PCG64(1050 + S))
+    K = 5
+    grid = np.cumsum(rng.uniform(0.5, 1.5, S)).astype(np.float32)
+    amp, var = rng.uniform(0.1, 1.0, (S, K)).astype(np.float32), rng.uniform(0.1, 2.0, (S, K)).astype(np.float32)
+    at = sorted({0, 1, S // 2, max(0, S - 3), S - 2, S - 1})
+    sn = np.concatenate([grid[at], np.nextafter(grid[at], np.float32(0)),
+                         rng.uniform(grid[0], grid[-1], 9), [np.nextafter(grid[-1], np.float32(np.inf))]]).astype(np.float32)
+    n = len(sn)
+    gal = wl.draw_galaxies(rng, n, W, 0, r_e_range=(1.0, W / 8.0))
+    bad = (sn < grid[0]) | (sn > grid[-1])
+    s = np.clip(np.searchsorted(grid, sn, side="right") - 1, 0, S - 2)
+    t = ((sn.astype(np.float64) - grid[s]) / (grid[s + 1].astype(np.float64) - grid[s]))[:, None]
+    t = np.where(bad[:, None], 0.0, t)
+    psf = gfc.Psf(ctx, wl.psf_moffat_halo(64).astype(np.float32))
+    fam = gfc.SersicFamily(ctx, grid, amp, var)
+    mix = gfc.Mixture(ctx, np.full(n, K), (1 - t) * amp[s] + t * amp[s + 1], (1 - t) * var[s] + t * var[s + 1])
+    args = (gal.x, gal.y, gal.flux, gal.r_e, gal.e1, gal.e2)
+    gpu = _np(gfc.gfc_render_stamps_sersic(ctx, psf, fam, *args, sn, W))
+    ref = _np(gfc.gfc_render_stamps(ctx, psf, mix, *args, W, mix_id=np.arange(n, dtype=np.int32)))
+    assert np.isnan(gpu[bad]).all()
+    idx = np.flatnonzero(~bad)
+    _check(gpu, ref[idx], idx)
+    psf.close(); fam.close(); mix.close()
