@@ -316,7 +316,11 @@ def gfc_render_stamps_backward(ctx, psf, mix, x, y, flux, r_e, e1, e2, W, grad_o
         grad_amp = None
     elif grad_amp is None:
         grad_amp = torch.zeros((mix.n_tables, GFC_KMAX), dtype=torch.float32, device=dev)
-    ws = ctypes.c_void_p(workspace.data_ptr()) if workspace is not None else None
+    # torch's allocator keeps the scratch for the stream the call runs on; the
+    # library's own stream-ordered allocation took 13 us of host time a call
+    if workspace is None:
+        workspace = torch.empty(gfc_backward_workspace_bytes(n), dtype=torch.uint8, device=dev)
+    ws = ctypes.c_void_p(workspace.data_ptr())
     call("gfc_render_stamps_backward", ctx.handle, psf.handle, mix.handle, ctypes.byref(g), int(n),
          int(W), int(flags), ctypes.c_void_p(go.data_ptr()), ctypes.c_void_p(grad_params.data_ptr()),
          ctypes.c_void_p(grad_amp.data_ptr()) if grad_amp is not None else None, ws, _stream_ptr(ctx.device))

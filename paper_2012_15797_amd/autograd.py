@@ -38,10 +38,17 @@ class RenderStamps(torch.autograd.Function):
         gp, ga = api.gfc_render_stamps_backward(
             gctx, ctx.psf, ctx.mix, x, y, flux, r_e, e1, e2, ctx.W, grad_out.contiguous(),
             mix_id=ctx.mix_id, flags=ctx.flags, cd=ctx.cd, mix_amp=ctx.amp_keep)
-        r = r_e.to(gp.device, torch.float32)
-        grads = [gp[:, 0], gp[:, 1], gp[:, 2], gp[:, 3] / r, gp[:, 4], gp[:, 5]]
-        grads = [g.to(t.device, t.dtype).reshape(t.shape) if t.requires_grad else None
-                 for g, t in zip(grads, (x, y, flux, r_e, e1, e2))]
+        def grad(k, t):
+            if not t.requires_grad:
+                return None
+            g = gp.select(1, k)
+            if k == 3:  # the adjoint's is d/d log r_e
+                g = g / t.to(gp.device, torch.float32)
+            if t.device != g.device or t.dtype != g.dtype:
+                g = g.to(t.device, t.dtype)
+            return g if t.shape == g.shape else g.reshape(t.shape)
+
+        grads = [grad(k, t) for k, t in enumerate((x, y, flux, r_e, e1, e2))]
         g_amp = ga if ctx.has_amp else None
         return (None, None, None, None, None, None, *grads, g_amp)
 
