@@ -630,7 +630,7 @@ def main():
     roofline = dict(bound="alu", achieved=round(achieved_tflops, 3), peak=round(FP32_FMA_NONPACKED_TFLOPS, 2),
                     unit="TFLOP/s", frac=round(achieved_tflops / FP32_FMA_NONPACKED_TFLOPS, 4),
                     traffic=measured_traffic(),
-                    kernel="render_small_kernel<64, false, false, false>",
+                    kernel="render_small_kernel<64, false, false, false, false>",
                     flops_per_stamp=round(float(flops_stamp.mean()), 1),
                     peak_note="FP32 vector FMA peak without packed instructions: 256 CU x 4 SIMD x 16 lanes x "
                               "2 FLOP x 2.4 GHz",
@@ -1055,7 +1055,7 @@ def size_throughput(gfc, ctx, dev, refs, reps=5, settle=45, settle_ms=50.0):
                                                         amp_grad=False), reps)
     fl = workload_flops(g, cfg["mix"], 64, adjoint=True)
     rl = flops_roofline(fl, ms_k)
-    rl.update(kernel="render_bwd_small_kernel<64>", kernel_ms=round(ms_k, 4),
+    rl.update(kernel="render_bwd_split_kernel<2>", kernel_ms=round(ms_k, 4),
               frac_whole_call=flops_roofline(fl, ms)["frac"],
               note="achieved over the adjoint kernel's launch alone; frac_whole_call over the whole call, "
                    "amplitude-gradient reduction included")

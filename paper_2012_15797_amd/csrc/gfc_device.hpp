@@ -189,8 +189,9 @@ __device__ __forceinline__ Profile make_profile(const RenderArgs& p, float a, fl
 // Amplitude and variance of component k < G.K.  Sersic: interpolated between
 // the cell's two grid indices.  Composite: the disk's components with
 // amplitudes (1 - t) A_d, then the bulge's with t A_b and variances r^2 v_b.
+template <bool PROF>
 __device__ __forceinline__ float2 component_mix(const RenderArgs& p, const Galaxy& G, const Profile& f, int k) {
-  if (p.prof == kProfTable) return make_float2(p.amp[G.table * kKmax + k], p.var[G.table * kKmax + k]);
+  if (!PROF || p.prof == kProfTable) return make_float2(p.amp[G.table * kKmax + k], p.var[G.table * kKmax + k]);
   const float t0 = 1.f - f.t;
   if (p.prof == kProfSersic) {
     const int K = p.prof_k1, i = f.s * K + k;

@@ -54,7 +54,8 @@ struct SmallCfg {
 // PT: each galaxy names its (constant) PSF in p.psf_id, and the stamp takes
 // that PSF's spectrum and Gaussian from the tables (a serving batch mixes
 // PSFs); the one-PSF instantiations compile exactly as without it.
-template <int W, bool EIG, bool LZ, bool PT>
+// PROF: each galaxy has a mixture of its own (p.prof).
+template <int W, bool EIG, bool LZ, bool PT, bool PROF>
 __global__ void __launch_bounds__((SmallCfg<W, EIG>::BLOCK)) __attribute__((amdgpu_waves_per_eu(W == 128 ? 2 : 1)))
 render_small_kernel(RenderArgs p) {
   using C = SmallCfg<W, EIG>;
@@ -79,9 +80,9 @@ render_small_kernel(RenderArgs p) {
   if constexpr (C::WAVE1 && C::SPB > 1) slot = __builtin_amdgcn_readfirstlane(slot);  // keeps the stamp index scalar
   const int64_t stamp = (int64_t)blockIdx.x * C::SPB + slot;
   const bool live = stamp < p.n;
-  Galaxy G = load_galaxy<W, true>(p, live ? stamp : p.n - 1);
+  Galaxy G = load_galaxy<W, PROF>(p, live ? stamp : p.n - 1);
   Profile prof = {0.f, 0.f, 0, true};
-  if (p.prof != kProfTable) {
+  if constexpr (PROF) {
     const int64_t gs = live ? stamp : p.n - 1;
     prof = make_profile<(W < 64 ? W : 64)>(p, p.prof_a[gs], p.prof_b ? p.prof_b[gs] : 0.f);
     if (!prof.ok) {  // invalid galaxy: NaN stamp, counted
@@ -304,7 +305,7 @@ render_small_kernel(RenderArgs p) {
     float wak = 0.f;
     bool rk = false;
     if (lk < G.K) {
-      const float2 av = component_mix(p, G, prof, lk);
+      const float2 av = component_mix<PROF>(p, G, prof, lk);
       const float Ak = av.x;
       vk = av.y;
       const float wk = route_weight<W>(vk * trB, p.flags);
@@ -334,7 +335,7 @@ render_small_kernel(RenderArgs p) {
     float wak = 0.f;
     bool rk = false;
     if (l < G.K) {
-      const float2 av = component_mix(p, G, prof, l);
+      const float2 av = component_mix<PROF>(p, G, prof, l);
       const float Ak = av.x;
       vk = av.y;
       const float wk = route_weight<W>(vk * trB, p.flags);
@@ -735,7 +736,7 @@ render_small_kernel(RenderArgs p) {
   if (live && !G.ok && l == 0) atomicAdd(p.invalid, 1ull);
 }
 
-template <int W, bool EIG, bool LZ, bool PT>
+template <int W, bool EIG, bool LZ, bool PT, bool PROF>
 static hipError_t launch_small(const RenderArgs& args, hipStream_t stream) {
   using C = SmallCfg<W, EIG>;
   constexpr int64_t kMaxBlocks = 1 << 30;
@@ -758,7 +759,7 @@ static hipError_t launch_small(const RenderArgs& args, hipStream_t stream) {
     p.prof_b = args.prof_b ? args.prof_b + done : nullptr;
     p.n = chunk;
     const unsigned blocks = (unsigned)((chunk + C::SPB - 1) / C::SPB);
-    hipLaunchKernelGGL((render_small_kernel<W, EIG, LZ, PT>), dim3(blocks), dim3(C::BLOCK), 0, stream, p);
+    hipLaunchKernelGGL((render_small_kernel<W, EIG, LZ, PT, PROF>), dim3(blocks), dim3(C::BLOCK), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     done += chunk;
@@ -766,18 +767,26 @@ static hipError_t launch_small(const RenderArgs& args, hipStream_t stream) {
   return hipSuccess;
 }
 
+template <int W, bool PROF>
+static hipError_t launch_one_psf(const RenderArgs& args, hipStream_t stream) {
+  if (args.flags & kLanczos3)
+    return args.eig_J > 0 ? launch_small<W, true, true, false, PROF>(args, stream)
+                          : launch_small<W, false, true, false, PROF>(args, stream);
+  return args.eig_J > 0 ? launch_small<W, true, false, false, PROF>(args, stream)
+                        : launch_small<W, false, false, false, PROF>(args, stream);
+}
+
 template <int W>
 hipError_t launch_render_small(const RenderArgs& args, hipStream_t stream) {
-  const bool lz = (args.flags & kLanczos3) != 0;
-  if (args.psf_id) {  // per-galaxy constant PSFs (eig_J == 0)
-    if (args.eig_J > 0) return hipErrorInvalidValue;
-    return lz ? launch_small<W, false, true, true>(args, stream) : launch_small<W, false, false, true>(args, stream);
+  if (args.psf_id) {  // per-galaxy constant PSFs (eig_J == 0), mixtures from the tables
+    if (args.eig_J > 0 || args.prof != kProfTable) return hipErrorInvalidValue;
+    return (args.flags & kLanczos3) ? launch_small<W, false, true, true, false>(args, stream)
+                                    : launch_small<W, false, false, true, false>(args, stream);
   }
-  if (lz)
-    return args.eig_J > 0 ? launch_small<W, true, true, false>(args, stream)
-                          : launch_small<W, false, true, false>(args, stream);
-  return args.eig_J > 0 ? launch_small<W, true, false, false>(args, stream)
-                        : launch_small<W, false, false, false>(args, stream);
+  // Galaxies with mixtures of their own take instantiations of their own: as
+  // a test in the shared ones they cost the plain render 1.6% at 128 x 128
+  // (253.3 us against 249.2 for 10,000 large galaxies) and 0.5% below.
+  return args.prof != kProfTable ? launch_one_psf<W, true>(args, stream) : launch_one_psf<W, false>(args, stream);
 }
 
 template hipError_t launch_render_small<16>(const RenderArgs&, hipStream_t);

@@ -104,7 +104,7 @@ __device__ __forceinline__ void publish_galaxy(const RenderArgs& p, uint32_t wor
                       (uint32_t)G.K);
     d[3] = make_uint4(G.ok ? 1u : 0u, __builtin_bit_cast(uint32_t, lamq), 0u, 0u);
   }
-  if (lane < G.K) s_mix[lane] = component_mix(p, G, prof, lane);
+  if (lane < G.K) s_mix[lane] = component_mix<true>(p, G, prof, lane);
 }
 
 // The published galaxy, in scalar registers.
