@@ -29,8 +29,8 @@
 // LDS holds one stamp per CU.  32 bins per thread keep it within 128 registers,
 // and half a stamp at a time within 10 KB of LDS per wavefront, so four
 // wavefronts per SIMD are resident.  Whole calls, r_e 0.5..8 px, 8 components:
-// 20,000 stamps of 64 x 64 in 176 us, 5,000 of 128 x 128 in 171 us (195 us with
-// r_e 10..60 px), 500 of 256 x 256 with r_e 10..60 px in 112 us.  One lane per
+// 20,000 stamps of 64 x 64 in 173 us, 5,000 of 128 x 128 in 169 us (192 us with
+// r_e 10..60 px), 500 of 256 x 256 with r_e 10..60 px in 105 us.  One lane per
 // row and two per column with the whole g tile in LDS (two wavefronts per
 // SIMD) took 199 us at 64 and 315 us (439 us) at 128; a slab in device memory
 // took 353 us at 256.

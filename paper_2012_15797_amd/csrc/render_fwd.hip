@@ -674,7 +674,7 @@ render_small_kernel(RenderArgs p) {
         // lane with the neighbours in three 16-byte reads.  Taps outside the
         // stamp have weight zero: the rows beyond it are left out, the
         // columns beyond it are zeros beside the tile's rows.  5,001 stamps
-        // take 154 us; with a pass of its own over the stamps in memory they
+        // take 147 us; with a pass of its own over the stamps in memory they
         // took 331 us (182 us that pass).
         constexpr int T0 = q == 0 ? 0 : C::HR - 2;            // output rows whose taps are in
         constexpr int NT = q == 0 ? C::HR - 2 : C::HR + 2;

@@ -621,7 +621,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
       // columns to a lane: the neighbours along x are the next lanes'.  Rows
       // and columns outside the stamp are zeros.  Rows 126 and 127 wait for
       // the second half, which keeps rows 123..127 of the first in s_top.
-      // 2,000 stamps take 293 us (the plain render 252 us); with a pass of its
+      // 2,000 stamps take 274 us (the plain render 234 us); with a pass of its
       // own over the stamps in memory they took 490 us.
       float* tile = reinterpret_cast<float*>(s_buf);
       {
