@@ -653,7 +653,8 @@ def main():
             exp_cost_slots=c_exp, time_ms=round(t_model * 1e3, 4),
             frac=round(t_model / (avg_kern_ms * 1e-3), 4),
             note="time the algorithm's minimal VALU issue needs at the measured FMA rate, an exponential "
-                 "costing the measured slots beside FMAs; frac = that time / kernel time")
+                 "costing the measured slots beside FMAs; frac = that time / kernel time (above 1 where "
+                 "several components share a polynomial, or two wavefronts issue together)")
 
     parity = None
     if oracle_stamps:
