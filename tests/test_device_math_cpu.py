@@ -9,6 +9,7 @@
 - gfc::fft<N, SIGN>, the in-register FFTs of every kernel."""
 
 import os
+import re
 import shutil
 import subprocess
 
@@ -53,3 +54,39 @@ def test_register_fft_accuracy(tmp_path):
         assert float(err) < 4e-7, line
         assert int(bad) == 0, line
     assert seen == {(1 << e, s) for e in range(9) for s in (1, -1)}
+
+
+def _shift_phase_cmd():
+    return ["hipcc", "-std=c++17", "-O3", "--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang",
+            "-packed-fp32-ops", "-I", os.path.join(ROOT, "paper_2012_15797_amd", "csrc"), "-I",
+            os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "native", "shift_phase_check.hip")]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
+def test_shift_phase_accuracy(tmp_path):
+    """The phase of a whole shift at every stamp size.  Its argument hi + lo / pi:
+    lo / pi is the sum of two roundings of at most 2^-24 half turns each, itself
+    rounded three times and scaled by a float32 pi, so the argument is within
+    2^-46.  The phase: sincospi_poly's 1.5e-7 and one rounding, 2^-25."""
+    exe = tmp_path / "shift_phase_check"
+    subprocess.run([*_shift_phase_cmd(), "-o", str(exe)], check=True, capture_output=True, timeout=300)
+    lines = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=300).stdout.splitlines()
+    assert [int(line.split()[0]) for line in lines] == [16, 32, 64, 128, 256]
+    for line in lines:
+        _, arg, phase = line.split()
+        assert float(arg) < 2.0 ** -46, line
+        assert float(phase) < 1.5e-7 + 2.0 ** -25, line
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
+def test_shift_argument_is_not_contracted(tmp_path):
+    """On the device the sums and products of the argument are the ones that are
+    written: none may be fused with another (fused, p - (hi - bb) takes the
+    unrounded product and pe is counted twice, an error of up to 1.9e-7)."""
+    ir = tmp_path / "shift_arg.ll"
+    subprocess.run([*_shift_phase_cmd(), "--offload-device-only", "-S", "-emit-llvm", "-o", str(ir)], check=True,
+                   capture_output=True, timeout=300)
+    body = ir.read_text().split("shift_arg_kernel", 1)[1].split("\n}", 1)[0].splitlines()
+    ops = [line.split("=", 1)[1].split() for line in body if re.search(r"= f(add|sub|mul) ", line)]
+    assert len(ops) >= 10  # three products, seven sums
+    assert all(set(op).isdisjoint({"contract", "fast", "reassoc"}) for op in ops), ops
