@@ -90,3 +90,17 @@ def test_shift_argument_is_not_contracted(tmp_path):
     ops = [line.split("=", 1)[1].split() for line in body if re.search(r"= f(add|sub|mul) ", line)]
     assert len(ops) >= 10  # three products, seven sums
     assert all(set(op).isdisjoint({"contract", "fast", "reassoc"}) for op in ops), ops
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
+def test_flat_polynomial(tmp_path):
+    """The polynomial for 2^x on [-1, 0] that the flat components share: its
+    coefficients leave a relative error of 2.08e-9, without a bias that would
+    add up over bins (mean below a tenth of that)."""
+    exe = tmp_path / "flat_check"
+    cmd = [*_shift_phase_cmd()[:-1], os.path.join(ROOT, "tests", "native", "flat_check.hip"), "-o", str(exe)]
+    subprocess.run(cmd, check=True, capture_output=True, timeout=300)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=300).stdout.split()
+    worst, mean = (float(v) for v in out)
+    assert worst < 2.2e-9, worst
+    assert abs(mean) < 2.1e-10, mean
