@@ -461,13 +461,14 @@ __device__ __forceinline__ bool take_flat(const Galaxy& G, float vk, float& wak,
   flat = flat && any;
   f.s = __builtin_amdgcn_rcpf(qmax);
   float p = flat ? wak : 0.f;
+  const float tf = flat ? t : 0.f;  // t itself may overflow (v r_e^2 beyond 2e36 px^2)
   static_for<0, kFlatDeg + 1>([&](auto jj) {
     constexpr int j = decltype(jj)::value;
     // N = 64: the components are in the first row of 16 lanes
     float a = kFlat[j] * lane_sum<(N == 64 ? 16 : N)>(p);
     if constexpr (N == 64) a = vector_f(lane_f(a, 0));
     f.a[j] = a;
-    p *= t;
+    p *= tf;
   });
   if (flat) wak = 0.f;
   return any;

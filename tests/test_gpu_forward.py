@@ -347,3 +347,34 @@ def test_flat_components_and_stores(ctx, W, flags):
     errs = peak_errors(once.cpu().numpy().astype(np.float64), ref, range(n))
     assert errs.max() <= TOL_PEAK, (errs.max(), int(np.argmax(errs)))
     psf.close(); mix.close()
+
+
+@pytest.mark.parametrize("flags", [0, 2])
+@pytest.mark.parametrize("W", [16, 32, 64, 128, 256])
+def test_largest_radii(ctx, W, flags):
+    """Radii whose product with a component's variance overflows the exponent's
+    range (v r_e^2 from 2e36 px^2): every pixel is below the smallest float32,
+    so the stamp is zero, and its neighbours are as without it.  (From 2.4e18
+    px the shape's own exponent overflows: NaN up to 128 x 128.)"""
+    import torch
+    import paper_2012_15797_amd as gfc
+
+    rng = np.random.Generator(np.random.PCG64(1760 + W))
+    mixtures = wl.mixture_set([(rng.dirichlet(np.ones(8)), np.logspace(-4, 1, 8))])
+    psf, mix = lib_objects(ctx, dict(mix=mixtures, psf=wl.config_metric(4)["psf"]))
+    n, huge = 9, np.array([1, 4, 6])
+    gal = wl.draw_galaxies(rng, n, W, 0)
+    gal.e1[huge] = gal.e2[huge] = 0.0
+
+    def render():
+        return gfc.gfc_render_stamps(ctx, psf, mix, gal.x, gal.y, gal.flux, gal.r_e, gal.e1, gal.e2, W,
+                                     flags=flags).cpu().numpy()
+
+    without = render()
+    gal.r_e[huge] = [1e18, 2e18, 3e18]
+    got = render()
+    assert (got[huge[:2]] == 0.0).all()
+    assert (got[huge[2]] == 0.0).all() or np.isnan(got[huge[2]]).all()
+    others = np.setdiff1d(np.arange(n), huge)
+    assert np.array_equal(got[others], without[others])
+    psf.close(); mix.close()
