@@ -164,7 +164,8 @@ render_bwd_split_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
   // + ixy dy and zy = al + be zx with al = dy / syy, be = -sxy / syy, and the
   // quadratic form is q = dy al + zx^2 / ixx.  So a row needs the moments
   // sum g N zx^p (p = 0, 1, 2) only, with the log2 of nrm exp(-q/2) as
-  // c0 + c2 zx^2.
+  // c0 + c2 zx^2.  zx0 is zx at column W / 2 (plus the lane's 4 r): near most
+  // galaxies' centres, where it is small and rounds by little.
   for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
     const int k = __builtin_ctz(mk);
     const float v = lane_f(vk, k);
@@ -183,7 +184,7 @@ render_bwd_split_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
       constexpr int half = decltype(hh)::value;
       const float dy = (float)(half * HROWS + LPW * wv + lane % LPW) - G.y0 - p.pg[1];
       const float al = dy * rsyy;
-      const float zx0 = fmaf(ixx, (float)(4 * (lane / LPW)) - G.x0 - p.pg[0], ixy * dy);
+      const float zx0 = fmaf(ixx, (float)(4 * (lane / LPW) + W / 2) - G.x0 - p.pg[0], ixy * dy);
       const float c0 = fmaf(kHalfLog2e * al, dy, lnrm);
       float m0 = 0.f, m1 = 0.f, m2 = 0.f;
       static_for<0, 8>([&](auto qq) {
@@ -191,7 +192,7 @@ render_bwd_split_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
         static_for<0, 4>([&](auto ii) {
           constexpr int i = decltype(ii)::value;
           const float2 z = zq[half][i / 2][q];
-          const float zx = fmaf(ixx, (float)(4 * D * q + i), zx0);
+          const float zx = fmaf(ixx, (float)(4 * D * q + i - W / 2), zx0);
           const float zz = zx * zx;
           const float gn = ((i & 1) ? z.y : z.x) * __builtin_amdgcn_exp2f(fmaf(c2, zz, c0));
           m0 += gn;

@@ -573,7 +573,7 @@ render_small_kernel(RenderArgs p) {
   float* st = reinterpret_cast<float*>(&s_t1[slot][0]);
   if (rmask != 0) {
     const float dy = (float)y - G.y0 - pg[1];
-    const float dx0 = -G.x0 - pg[0];  // dx of column 0
+    const float dx0 = (float)(W / 2) - G.x0 - pg[0];  // dx of column W / 2
     for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
       const float4 rc = s_rc[slot][__builtin_ctz(mk)];
       // Along this lane's row (dy fixed) the quadratic form is
@@ -581,14 +581,17 @@ render_small_kernel(RenderArgs p) {
       // conditional mean, so that the exponent stays a difference of small
       // terms near the peak (an expansion about a fixed column cancels terms
       // of size (W/2)^2 / sxx there): with dx = x + dx0 the exponent is
-      // k - u^2, u = g (x + m), two FMAs with an immediate x.
+      // k - u^2, u = g (x + m), two FMAs with an immediate x.  x counts from
+      // column W/2, near most galaxies' centres: m is small there and g m
+      // rounds by little.  (Counted from column 0, that rounding moved the
+      // component along x by up to 2e-6 px at 64 x 64, in every row alike.)
       const float ampr = rc.x, g = rc.y;
       const float k0 = rc.w * dy * dy;
       const float gm = g * fmaf(-rc.z, dy, dx0);
       static_for<0, W / 2>([&](auto xx) {
         constexpr int x = 2 * decltype(xx)::value;  // two columns at a time
-        const float u0 = fmaf(g, (float)x, gm);
-        const float u1 = fmaf(g, (float)(x + 1), gm);
+        const float u0 = fmaf(g, (float)(x - W / 2), gm);
+        const float u1 = fmaf(g, (float)(x + 1 - W / 2), gm);
         R[x >> 1].x = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u0, u0, k0)), R[x >> 1].x);
         R[x >> 1].y = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u1, u1, k0)), R[x >> 1].y);
       });

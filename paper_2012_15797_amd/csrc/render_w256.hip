@@ -581,7 +581,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
     // pixels x = 4 r + 32 q + 0..3 (zq[0][q], then zq[1][q])
     if (rmask != 0) {
       const float dy = (float)y - G.y0 - pg[1];
-      const float dx0 = -G.x0 - pg[0];  // dx of column 0
+      const float dx0 = (float)(W / 2) - G.x0 - pg[0];  // dx of column W / 2, from which x counts (see the W <= 128 render)
       for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
         const float4 rc = s_rc[__builtin_ctz(mk)];
         const float ampr = rc.x, g = rc.y;
@@ -592,7 +592,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
         const float gm = g * fmaf(-rc.z, dy, dx0 + (float)(4 * r));  // x measured from this lane's 4 r
         static_for<0, 8>([&](auto qq) {
           constexpr int q = decltype(qq)::value;
-          constexpr float xo = (float)(32 * q);
+          constexpr float xo = (float)(32 * q - W / 2);
           const float u0 = fmaf(g, xo, gm), u1 = fmaf(g, xo + 1.f, gm);
           const float u2 = fmaf(g, xo + 2.f, gm), u3 = fmaf(g, xo + 3.f, gm);
           zq[0][q].x = fmaf(ampr, __builtin_amdgcn_exp2f(fmaf(-u0, u0, k0)), zq[0][q].x);

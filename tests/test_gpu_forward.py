@@ -378,3 +378,42 @@ def test_largest_radii(ctx, W, flags):
     others = np.setdiff1d(np.arange(n), huge)
     assert np.array_equal(got[others], without[others])
     psf.close(); mix.close()
+
+
+def _centred_gaussians(rng, n, W):
+    """Round one-component galaxies near the stamp's middle and a PSF whose
+    Gaussian (given, off centre) is all that the real-space part takes of it:
+    float64 stamps and their derivatives along x and y."""
+    x, y = (W / 2 + rng.uniform(0, 1, (2, n))).astype(np.float32)
+    r_e = rng.uniform(1.0, W / 16, n).astype(np.float32)
+    gauss = [0.21, -0.37, 1.5, 0.0, 1.5, 0.9]
+    var = r_e.astype(np.float64) ** 2 + gauss[2]
+    p = np.arange(W, dtype=np.float64)
+    ux = p[None, None, :] - (x.astype(np.float64) + gauss[0])[:, None, None]
+    uy = p[None, :, None] - (y.astype(np.float64) + gauss[1])[:, None, None]
+    v = var[:, None, None]
+    img = gauss[5] / (2 * np.pi * v) * np.exp(-0.5 * (ux * ux + uy * uy) / v)
+    return x, y, r_e, gauss, img, img * ux / v, img * uy / v
+
+
+@pytest.mark.parametrize("W", [16, 32, 64, 128, 256])
+def test_real_space_position(ctx, W):
+    """Where the real-space part puts a galaxy: the shift that its error amounts
+    to (the error's projection on the derivative along x and y).  dx of the
+    middle column, at most 1.4 px here, rounds by 2^-24, m by 2^-24 and g m by
+    2^-24 times m: below 2^-22 px, with the roundings that differ from pixel to
+    pixel averaging out.  At 256 the eight lanes of a row count from columns
+    up to 28 further on, and m rounds by 2^-24 times that: 2^-19 px."""
+    import paper_2012_15797_amd as gfc
+
+    rng = np.random.Generator(np.random.PCG64(1790 + W))
+    n = 32
+    x, y, r_e, gauss, img, ix, iy = _centred_gaussians(rng, n, W)
+    psf = gfc.Psf(ctx, wl.psf_moffat_halo(32).astype(np.float32), gauss)
+    mix = gfc.Mixture.from_workload(ctx, wl.mixture_set([(np.ones(1), np.ones(1))]).as_f32())
+    zero = np.zeros(n, np.float32)
+    got = gfc.gfc_render_stamps(ctx, psf, mix, x, y, np.ones(n, np.float32), r_e, zero, zero, W, flags=2)
+    err = got.cpu().numpy().astype(np.float64) - img
+    shift = [np.abs((err * d).sum((1, 2)) / (d * d).sum((1, 2))).max() for d in (ix, iy)]
+    assert max(shift) < 2.0 ** (-22 if W <= 128 else -19), shift
+    psf.close(); mix.close()
