@@ -8,6 +8,37 @@
 
 namespace gfc {
 
+// Column c of a real image's row spectra from rows transformed as W / 2 packed
+// values Z, times the column's phase exp(2 pi i (n + f) c / W) and its weight:
+//   pc (e + tw d),  e, d = Z[c] +- conj Z[W/2 - c],  tw = -i exp(-2 pi i c / W).
+// Weight: h(k_x) / W^2 with h = 1 on column 0 and 2 elsewhere, halved for the
+// factor 2 in e + tw d.  Columns 0 and W / 2 are real, 2 (Re +- Im) of Z[0],
+// and are taken together, the second times i: 2 (1 + i) conj Z[0] (phase 1).
+// The phase multiplies last, by itself.  Folded with tw into one factor each
+// of Z[c] and conj Z[W/2 - c] it saves four multiply-adds in twelve, but the
+// factors then are sums of size one to two, which round the small phases of
+// the low columns by 2.2e-8 rms instead of 1.1e-8, in every row alike: the x
+// gradient of a fit's step erred by 1.3-1.65 times as much.
+struct ColumnSplit {
+  float2 tw, pc;
+  GFC_HD float2 at(float2 zc, float2 zr) const {  // zr = Z[(W/2 - c) mod W/2]
+    const float2 b = cconj(zr);
+    return cmul(cfma(tw, csub(zc, b), cadd(zc, b)), pc);
+  }
+};
+
+// wc = exp(-2 pi i c / W)
+template <int W>
+GFC_HD ColumnSplit column_split(float f, int n, int c, float2 wc) {
+  constexpr float wt = 1.f / ((float)W * (float)W);
+  float s, co;
+  shift_phase<W>(f, n, c, &s, &co);
+  ColumnSplit r;
+  r.tw = c == 0 ? make_float2(-1.f, 0.f) : rot90<-1>(wc);
+  r.pc = c == 0 ? make_float2(0.5f * wt, 0.5f * wt) : make_float2(co * wt, -s * wt);
+  return r;
+}
+
 // Contributions of mixture component k to the chain rule (dx, dy, dF and the
 // three entries of dL/dB), and its amplitude partial written to ap[k].
 // pk_sum[k * pk_stride]: the component's Fourier sum p_k; racc[k racc_stride + i]: its

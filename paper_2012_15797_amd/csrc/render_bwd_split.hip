@@ -218,30 +218,13 @@ render_bwd_split_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
   const int c = D == 8 ? t >> 3 : wv * LPW + lane % LPW;
   const int h = D == 8 ? t & 7 : lane / LPW;
   const float nu = (float)c * (1.f / W);
-  // The real-input split while reading the transformed rows is Gr2[c] = e + t,
-  // e = Z[c] + conj Z[NC - c], t = tw (Z[c] - conj Z[NC - c]), tw = -i w^{-c}:
-  // with the column's phase and its weight, A Z[c] + B conj Z[NC - c], A and B
-  // = (1 +- tw) conj(phase) weight.  Weight: h(k_x) / W^2 with h = 1 on column
-  // 0 and 2 elsewhere, halved for the factor 2 in Gr2.  Columns 0 and NC are
-  // real, 2 (Re +- Im) of Z[0], and are taken together as Gr2[0] + i Gr2[NC] =
-  // 2 (1 + i) conj Z[0] (phase 1).  The second never needs to be taken out of
-  // column 0 again: every sum over the bins below is the real part of a sum of
-  // terms that are Hermitian in k_y on column 0 (a real column's transform
-  // times the PSF's, the phases and real even factors), to which i times
-  // another such column adds nothing.
-  float2 cA, cB;
-  {
-    float sx, cx;
-    shift_phase<W>(G.fx, G.nx, c, &sx, &cx);
-    const float2 px = cscale(make_float2(cx, sx), 1.f / ((float)W * (float)W));
-    const float2 tw = rot90<-1>(twiddle_rt<-1, W>(c));
-    cA = cmulc(make_float2(1.f + tw.x, tw.y), px);
-    cB = cmulc(make_float2(1.f - tw.x, -tw.y), px);
-    if (c == 0) {
-      cA = make_float2(0.f, 0.f);
-      cB = make_float2(1.f / ((float)W * (float)W), 1.f / ((float)W * (float)W));
-    }
-  }
+  // The real-input split, the column's phase and its weight are applied while
+  // reading the transformed rows.  The packed column NC never needs to be taken
+  // out of column 0 again: every sum over the bins below is the real part of a
+  // sum of terms that are Hermitian in k_y on column 0 (a real column's
+  // transform times the PSF's, the phases and real even factors), to which i
+  // times another such column adds nothing.
+  const ColumnSplit split = column_split<W>(G.fx, G.nx, c, twiddle_rt<-1, W>(c));
   float2 X4[K4][D];                         // row spectra: X4[k][q] of row D k + h + 32 q, column c
   static_for<0, 2>([&](auto hh) {
     constexpr int half = decltype(hh)::value;
@@ -298,10 +281,7 @@ render_bwd_split_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
         static_for<0, D / 2>([&](auto qq) {
           constexpr int q = decltype(qq)::value;
           const float2* rw = s_buf + (D * k + h + 32 * q) * TS;
-          const float2 a = rw[c], b = rw[cb];
-          X4[k][(D / 2) * half + q] =
-              make_float2(fmaf(cA.x, a.x, fmaf(-cA.y, a.y, fmaf(cB.x, b.x, cB.y * b.y))),
-                          fmaf(cA.x, a.y, fmaf(cA.y, a.x, fmaf(cB.y, b.x, -(cB.x * b.y)))));
+          X4[k][(D / 2) * half + q] = split.at(rw[c], rw[cb]);
         });
         if constexpr ((k + 1) * D % 8 == 0) __builtin_amdgcn_sched_barrier(0);
       });

@@ -104,3 +104,22 @@ def test_flat_polynomial(tmp_path):
     worst, mean = (float(v) for v in out)
     assert worst < 2.2e-9, worst
     assert abs(mean) < 2.1e-10, mean
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
+def test_column_split_phase(tmp_path):
+    """The column phases of the adjoint from 64 up.  An error that a column's
+    rows have in common moves the galaxy along x: it is that of the phase
+    itself, 1.1e-8 rms at the low columns, that of tw (a float32 rounding,
+    1.7e-8 rms) on the half of the sum that it multiplies, and the 64 rows' own
+    roundings of 3e-8 averaged, 0.4e-8: together 1.4e-8.  Column 0, packed with
+    column W / 2: four roundings."""
+    exe = tmp_path / "column_split_check"
+    cmd = [*_shift_phase_cmd()[:-1], os.path.join(ROOT, "tests", "native", "column_split_check.hip"), "-o", str(exe)]
+    subprocess.run(cmd, check=True, capture_output=True, timeout=300)
+    lines = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=300).stdout.splitlines()
+    assert [int(line.split()[0]) for line in lines] == [64, 128, 256]
+    for line in lines:
+        _, rms, worst0 = line.split()
+        assert float(rms) < 1.6e-8, line
+        assert float(worst0) < 4 * 2.0 ** -24, line
