@@ -317,10 +317,15 @@ def gfc_render_stamps_backward(ctx, psf, mix, x, y, flux, r_e, e1, e2, W, grad_o
     elif grad_amp is None:
         grad_amp = torch.zeros((mix.n_tables, GFC_KMAX), dtype=torch.float32, device=dev)
     # torch's allocator keeps the scratch for the stream the call runs on; the
-    # library's own stream-ordered allocation took 13 us of host time a call
+    # library's own stream-ordered allocation took 13 us of host time a call.
+    # Where torch has no memory left the library allocates after all, and
+    # reports GFC_ENOMEM if it cannot either.
     if workspace is None:
-        workspace = torch.empty(gfc_backward_workspace_bytes(n), dtype=torch.uint8, device=dev)
-    ws = ctypes.c_void_p(workspace.data_ptr())
+        try:
+            workspace = torch.empty(gfc_backward_workspace_bytes(n), dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:
+            pass
+    ws = ctypes.c_void_p(workspace.data_ptr()) if workspace is not None else None
     call("gfc_render_stamps_backward", ctx.handle, psf.handle, mix.handle, ctypes.byref(g), int(n),
          int(W), int(flags), ctypes.c_void_p(go.data_ptr()), ctypes.c_void_p(grad_params.data_ptr()),
          ctypes.c_void_p(grad_amp.data_ptr()) if grad_amp is not None else None, ws, _stream_ptr(ctx.device))

@@ -356,3 +356,40 @@ def test_amplitude_sums_in_one_launch(ctx, n, n_tables):
     np.add.at(scale, mid, np.abs(per_gal))
     assert (np.abs(got - ref) <= 44 * 2.0 ** -24 * scale).all()
     psf.close(); own.close(); mix.close()
+
+
+def test_workspace_when_torch_has_no_memory(ctx, monkeypatch):
+    """With nothing left in torch's allocator for the adjoint's scratch the
+    library allocates it: the call gives the same gradients, and a failure is
+    the library's own (GfcError)."""
+    import torch
+    import paper_2012_15797_amd as gfc
+    from paper_2012_15797_amd import api
+
+    rng = np.random.Generator(np.random.PCG64(1850))
+    cfg = wl.config_metric(10)
+    n, W = 70, 32
+    gal = wl.draw_galaxies(rng, n, W, 0)
+    g = torch.as_tensor(rng.standard_normal((n, W, W)).astype(np.float32)).cuda()
+    psf = gfc.Psf(ctx, cfg["psf"])
+    mix = gfc.Mixture.from_workload(ctx, cfg["mix"].as_f32())
+
+    def adjoint():
+        out = gfc.gfc_render_stamps_backward(ctx, psf, mix, gal.x, gal.y, gal.flux, gal.r_e, gal.e1, gal.e2, W, g)
+        torch.cuda.synchronize()
+        return [t.cpu() for t in out]
+
+    usual = adjoint()
+    empty, refused = torch.empty, []
+
+    def no_scratch(*args, **kwargs):
+        if kwargs.get("dtype") is torch.uint8:
+            refused.append(args)
+            raise torch.OutOfMemoryError("no memory left")
+        return empty(*args, **kwargs)
+
+    monkeypatch.setattr(api.torch, "empty", no_scratch)
+    got = adjoint()
+    assert refused
+    assert all(torch.equal(a, b) for a, b in zip(usual, got))
+    psf.close(); mix.close()
