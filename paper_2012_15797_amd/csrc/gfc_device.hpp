@@ -31,6 +31,7 @@ struct RenderArgs {
   const int32_t* K;        // [n_tables]
   int n_tables;
   int kmax;                // max K over the tables
+  float flat_v2;           // the second smallest variance of a table, the largest over the tables (see flat_shared)
   float cdinv[4];          // CD^{-1}, row-major (identity by default)
   float pg[6];             // PSF Gaussian: mu_x, mu_y, c_xx, c_xy, c_yy, amp
   const float2* psf_main;  // PSF spectrum, lane-permuted columns 0..W/2-1
@@ -445,6 +446,23 @@ struct FlatSum {
     return r;
   }
 };
+
+// Whether stamps that share a wavefront (W < 64) look for flat components: if
+// every table has two with v W^2 <= 1.1, flat up to r_e = W / 4, where a round
+// galaxy has qmax = 0.89 W^2.  A component leaves the wavefront's loop only if
+// it is flat in all of its stamps, while one stamp's sum costs every lane the
+// polynomial.  It is a rule on the launch's tables, so that a stamp's values
+// do not depend on its neighbours.  Times without and with the polynomial,
+// r_e 0.5..8 px, 60,000 stamps of 16 x 16 and 30,000 of 32 x 32: eight
+// components from 1e-4 r_e^2 30.4 -> 30.6 and 47.0 -> 46.1 us, sixteen 43.4 ->
+// 41.0 and 69.5 -> 60.8 us, eight below 1e-5 24.3 -> 19.0 and 41.0 -> 33.3 us;
+// where the rule says no, six from 1e-3 26.2 -> 28.4 and 41.9 -> 43.9 us, six
+// from 0.02 28.0 -> 30.3 and 43.7 -> 45.8 us, and tables of both kinds mixed
+// 28.2 -> 29.5 and 45.0 -> 44.9 us.
+template <int W>
+__device__ __forceinline__ bool flat_shared(const RenderArgs& p) {
+  return p.flat_v2 * (float)(W * W) <= 1.1f;
+}
 
 // Lane k of each group of N lanes holds component k's variance vk and Fourier
 // amplitude wak (w A; zero past the table's K).  With two or more flat

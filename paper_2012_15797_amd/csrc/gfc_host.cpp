@@ -6,6 +6,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <limits>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -118,6 +119,7 @@ gfc_status fill_render_args(gfc_ctx* ctx, gfc_psf* psf, const gfc_mix* mix, cons
   a->K = mix->d_K;
   a->n_tables = mix->n_tables;
   a->kmax = mix->kmax;
+  a->flat_v2 = mix->v2;
   if (gal->cd) {
     const double t = gal->cd[0], u = gal->cd[1], v = gal->cd[2], w = gal->cd[3];
     const double det = t * w - u * v;
@@ -150,6 +152,14 @@ gfc_status fill_render_args(gfc_ctx* ctx, gfc_psf* psf, const gfc_mix* mix, cons
   a->flags = flags;
   a->invalid = ctx->d_invalid;
   return GFC_OK;
+}
+
+void two_smallest(const float* var, int n, float out[2]) {
+  out[0] = out[1] = std::numeric_limits<float>::infinity();
+  for (int k = 0; k < n; ++k) {
+    out[1] = std::min(out[1], std::max(out[0], var[k]));
+    out[0] = std::min(out[0], var[k]);
+  }
 }
 
 void attach_spectrum(RenderArgs* a, const PsfSpectrum* spec) {
@@ -463,6 +473,11 @@ gfc_status gfc_mix_create(gfc_ctx* ctx, int n_tables, const int* K, const float*
   mix->n_tables = n_tables;
   mix->kmax = kmax;
   mix->K.assign(K, K + n_tables);
+  mix->low.resize(2 * (size_t)n_tables);
+  for (int t = 0; t < n_tables; ++t) {
+    two_smallest(&v[(size_t)t * GFC_KMAX], K[t], &mix->low[2 * (size_t)t]);
+    mix->v2 = std::max(mix->v2, mix->low[2 * (size_t)t + 1]);
+  }
   const size_t nb = (size_t)n_tables * GFC_KMAX * sizeof(float);
   hipError_t e = hipMalloc(&mix->d_amp, nb);
   if (e == hipSuccess) e = hipMalloc(&mix->d_var, nb);

@@ -53,6 +53,8 @@ struct gfc_mix {
   float* d_var = nullptr;
   int32_t* d_K = nullptr;
   std::vector<int32_t> K;  // host copy of the component counts
+  std::vector<float> low;  // [n_tables][2]: each table's two smallest variances (+inf where it has one)
+  float v2 = 0.f;          // the largest of the second ones
 };
 
 namespace gfc {
@@ -81,6 +83,8 @@ const PsfSpectrum* psf_cache_find(gfc_psf* psf, int W);
 gfc_status noalloc_scratch_setup(int device);
 gfc_status fill_render_args(gfc_ctx* ctx, gfc_psf* psf, const gfc_mix* mix, const gfc_galaxies* gal,
                             int64_t n, int W, unsigned flags, RenderArgs* a);
+// The two smallest of n variances (+inf where there are fewer).
+void two_smallest(const float* var, int n, float out[2]);
 // Points the render arguments at a cached spectrum.
 void attach_spectrum(RenderArgs* a, const PsfSpectrum* spec);
 // Launches the forward kernels for stamp size W (arguments already validated).

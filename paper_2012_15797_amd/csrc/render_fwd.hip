@@ -346,13 +346,21 @@ render_small_kernel(RenderArgs p) {
     const unsigned long long rb = __ballot(rk);
     rmask = (unsigned)(rb >> ((int)__lane_id() & ~(W - 1))) & (unsigned)((1ull << W) - 1ull);
     FlatSum f;
-    take_flat<W>(G, vk, wak, f);
-    flat_terms(f);
+    const bool flat = flat_shared<W>(p);  // uniform
+    if (flat) take_flat<W>(G, vk, wak, f);
     // over the components that any of the wavefront's stamps still needs
     unsigned long long need = __ballot(wak != 0.f);
     need |= need >> 32;
     if constexpr (W == 16) need |= need >> 16;
-    for (unsigned mk = (unsigned)need & ((1u << kKmax) - 1u); mk != 0; mk &= mk - 1) {
+    unsigned mk = (unsigned)need & ((1u << kKmax) - 1u);
+    if (flat) {
+      flat_terms(f);
+    } else {
+      const int k = mk ? __builtin_ctz(mk) : 0;
+      first_terms(__shfl(vk, k, W), __shfl(wak, k, W));
+      mk &= mk - 1;
+    }
+    for (; mk != 0; mk &= mk - 1) {
       const int k = __builtin_ctz(mk);
       const float wa = __shfl(wak, k, W);
       if (wa == 0.f) continue;

@@ -417,3 +417,32 @@ def test_real_space_position(ctx, W):
     shift = [np.abs((err * d).sum((1, 2)) / (d * d).sum((1, 2))).max() for d in (ix, iy)]
     assert max(shift) < 2.0 ** (-22 if W <= 128 else -19), shift
     psf.close(); mix.close()
+
+
+@pytest.mark.parametrize("shared", [True, False])
+@pytest.mark.parametrize("W", [16, 32])
+def test_flat_components_between_neighbours(ctx, W, shared):
+    """Stamps that share a wavefront, with tables for which it forms the flat
+    components' polynomial and with one more table for which it does not: both
+    against the oracle, and each stamp is bit for bit the one that it is in a
+    launch of its own."""
+    import paper_2012_15797_amd as gfc
+
+    rng = np.random.Generator(np.random.PCG64(1880 + W))
+    tables = [(rng.dirichlet(np.ones(8)), np.logspace(-4, 1, 8)), (rng.dirichlet(np.ones(16)), np.logspace(-9, -5, 16)),
+              (np.array([0.9, 0.0, -0.2, 0.3]), np.array([2e-4, 1e-3, 1e-2, 0.5]))]
+    mixtures = wl.mixture_set(tables if shared else tables + [(np.array([0.5, 0.5]), np.array([3.0, 9.0]))])
+    cfg = dict(mix=mixtures, psf=wl.config_metric(4)["psf"])
+    n = 27
+    gal = wl.draw_galaxies(rng, n, W, (np.arange(n) % 3).astype(np.int32), r_e_range=(0.1, W / 2.0))
+    psf, mix = lib_objects(ctx, cfg)
+
+    def render(i):
+        return gfc.gfc_render_stamps(ctx, psf, mix, gal.x[i], gal.y[i], gal.flux[i], gal.r_e[i], gal.e1[i], gal.e2[i], W,
+                                     mix_id=gal.mix_id[i]).cpu().numpy()
+
+    got = render(np.arange(n))
+    assert np.array_equal(got, np.concatenate([render(np.array([i])) for i in range(n)]))
+    errs = peak_errors(got.astype(np.float64), oracle_stamps(cfg, gal, range(n)), range(n))
+    assert errs.max() <= TOL_PEAK, (errs.max(), int(np.argmax(errs)))
+    psf.close(); mix.close()
