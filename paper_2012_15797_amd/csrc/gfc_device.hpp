@@ -464,30 +464,43 @@ __device__ __forceinline__ bool flat_shared(const RenderArgs& p) {
   return p.flat_v2 * (float)(W * W) <= 1.1f;
 }
 
-// Lane k of each group of N lanes holds component k's variance vk and Fourier
-// amplitude wak (w A; zero past the table's K).  With two or more flat
-// components in a stamp (one costs the same either way), their amplitudes
-// move from wak into the sums f (every lane of the group); returns whether
-// the lane's stamp has such a sum.  N = 64: f in vector registers.
+// Lane k of each group of N lanes (for N = 64: of each row of 16) holds
+// component k's variance vk and Fourier amplitude wak (w A; zero past the
+// table's K).  With two or more flat components in a stamp (one costs the same
+// either way), their amplitudes move from wak into the sums f (every lane of
+// the group; zeros if the stamp has no such sum); returns whether the lane's
+// stamp has one.  N = 64: f in vector registers.
 template <int N>
 __device__ __forceinline__ bool take_flat(const Galaxy& G, float vk, float& wak, FlatSum& f) {
   const float qmax = fmaxf(-kQ * fmaf(0.25f, G.b11 + G.b22, 0.5f * fabsf(G.b12)), 1e-30f);
   const float t = vk * qmax;
   bool flat = t <= 1.f && wak != 0.f && finitef(wak);
-  const unsigned long long b = __ballot(flat) >> ((int)__lane_id() & ~(N - 1) & 63);
-  const bool any = __popcll(b & (N == 64 ? ~0ull : (1ull << (N & 63)) - 1ull)) >= 2;
+  constexpr int NK = N == 64 ? kKmax : N;
+  const unsigned b = (unsigned)(__ballot(flat) >> ((int)__lane_id() & ~(N - 1) & 63)) & (unsigned)((1ull << NK) - 1ull);
+  const bool any = __popc(b) >= 2;
   flat = flat && any;
   f.s = __builtin_amdgcn_rcpf(qmax);
   float p = flat ? wak : 0.f;
   const float tf = flat ? t : 0.f;  // t itself may overflow (v r_e^2 beyond 2e36 px^2)
-  static_for<0, kFlatDeg + 1>([&](auto jj) {
-    constexpr int j = decltype(jj)::value;
-    // N = 64: the components are in the first row of 16 lanes
-    float a = kFlat[j] * lane_sum<(N == 64 ? 16 : N)>(p);
-    if constexpr (N == 64) a = vector_f(lane_f(a, 0));
-    f.a[j] = a;
-    p *= tf;
-  });
+  if constexpr (N == 64) {
+    // Row r forms the sums j = r and 4 + r: two sums over 16 lanes in place of
+    // seven.  (The sums are paid with no flat component too: at 256 x 256, one
+    // to six components, seven cost 1.5-3% of the render.)
+    const int r = (int)__lane_id() >> 4;
+    const float t2 = tf * tf;
+    p = (r & 1) ? p * tf : p;
+    p = (r & 2) ? p * t2 : p;
+    const float s0 = lane_sum<16>(p), s1 = lane_sum<16>(p * (t2 * t2));
+    static_for<0, kFlatDeg + 1>([&](auto jj) {
+      constexpr int j = decltype(jj)::value;
+      f.a[j] = kFlat[j] * vector_f(lane_f(j < 4 ? s0 : s1, 16 * (j & 3)));
+    });
+  } else {
+    static_for<0, kFlatDeg + 1>([&](auto jj) {
+      f.a[decltype(jj)::value] = kFlat[decltype(jj)::value] * lane_sum<N>(p);
+      p *= tf;
+    });
+  }
   if (flat) wak = 0.f;
   return any;
 }

@@ -299,9 +299,9 @@ render_small_kernel(RenderArgs p) {
     });
   };
   if constexpr (C::WAVE1) {
-    // One stamp per wavefront: lane k works out the route weight of component
-    // k once (K <= 16 lanes), and the loop takes v and w A from lane k.
-    const int lk = (int)__lane_id();
+    // One stamp per wavefront: lane k of each row of 16 works out the route
+    // weight of component k once, and the loop takes v and w A from lane k.
+    const int lk = (int)__lane_id() & (kKmax - 1);
     float wak = 0.f;
     bool rk = false;
     if (lk < G.K) {
@@ -313,10 +313,10 @@ render_small_kernel(RenderArgs p) {
       rk = wk < 1.f && Ak != 0.f;
       rak = (1.f - wk) * Ak;
     }
-    rmask = (unsigned)__ballot(rk);
+    rmask = (unsigned)__ballot(rk) & ((1u << kKmax) - 1u);
     FlatSum f;
     const bool flat = take_flat<64>(G, vk, wak, f);  // uniform
-    unsigned mk = (unsigned)__ballot(wak != 0.f);
+    unsigned mk = (unsigned)__ballot(wak != 0.f) & ((1u << kKmax) - 1u);
     if (flat) {
       flat_terms(f);
     } else {

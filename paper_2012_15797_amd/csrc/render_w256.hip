@@ -297,13 +297,13 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
   const float vmaxN = uniform_f(kSkipLog2 * __builtin_amdgcn_rcpf(lamq * 0.25f));  // |nu| = 1/2 or |omega| = 1/2
   float S[M];
   float SN[3] = {0.f, 0.f, 0.f};
-  // Lane k of every wavefront works out component k's route weight (K <= 16
-  // lanes), the loop takes v and w A from it by lane reads, and lane k of
-  // the first wavefront forms the component's real-space constants.
+  // Lane k of every wavefront (of each row of 16 lanes) works out component
+  // k's route weight, the loop takes v and w A from it by lane reads, and lane
+  // k of the first wavefront forms the component's real-space constants.
   float vk = 0.f, wak = 0.f;
   bool rk = false;
   {
-    const int lk = lane;
+    const int lk = lane & (kKmax - 1);
     if (lk < G.K) {
       const float2 av = s_mix[lk];
       const float Ak = av.x;
@@ -333,7 +333,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
   } else {
     static_for<0, M>([&](auto mm) { S[decltype(mm)::value] = 0.f; });
   }
-  for (unsigned mk = (unsigned)__ballot(wak != 0.f); mk != 0; mk &= mk - 1) {
+  for (unsigned mk = (unsigned)__ballot(wak != 0.f) & ((1u << kKmax) - 1u); mk != 0; mk &= mk - 1) {
     const int k = __builtin_ctz(mk);
     const float vs = lane_f(vk, k);  // compared as an integer (both positive): a scalar compare
     const float wa = vector_f(lane_f(wak, k)), v = vector_f(vs);
