@@ -74,11 +74,12 @@ struct Split {
   static constexpr int BUF = HROWS * TS;
   // after the column exchange: phases, packed Nyquist column and twins
   // behind its slots, later the p_k partials
-  static constexpr int PY = NWAVE * LPW * CXS, NYQ = PY + W + 2, UX = NYQ + W;
   static constexpr int PKS = BLOCK + BLOCK / kKmax;       // floats per component of the p_k partials
-  static_assert(UX + NC <= BUF && kKmax * PKS <= 2 * BUF, "the overlays fit in the half buffer");
-  // the twins are read while other wavefronts may already write partials
-  static_assert(NWAVE == 1 || kKmax * PKS <= 2 * UX, "the twins lie behind the partials");
+  static constexpr int PY = NWAVE * LPW * CXS, NYQ = PY + W + 2;
+  // the twins lie behind the partials too: they are read while other lanes may
+  // already write partials
+  static constexpr int UX = std::max(NYQ + W, kKmax * PKS / 2);
+  static_assert(UX + NC <= BUF && kKmax * PKS <= 2 * UX, "the overlays fit in the half buffer");
   static_assert(LPW * RXS <= LPW * TS, "a row exchange slice lies in its wavefront's rows");
   static constexpr int TWC = 33, TWR = N1 + 1;            // rows of the twiddle tables
 };
