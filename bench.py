@@ -93,6 +93,31 @@ def algorithmic_flops_per_stamp(W, kf, kr):
     return n_eval * (4.0 + 4.0 * kf) + 14.0 * H + 2.5 * W * W * math.log2(W * W) + 7.0 * W * W * kr
 
 
+def flat_counts(gal, var, W, tables=None):
+    """Components per galaxy whose exponent stays within one power of two over
+    the frequency grid (v qmax <= 1, qmax at a corner of the grid), where there
+    are two or more: the forward sums them as one polynomial.  At 16 and 32 it
+    does so where every table (tables: the variances of each; var alone if not
+    given) has two with v W^2 <= 1.1."""
+    var = np.asarray(var, np.float64)
+    if W < 64 and any(len(t) < 2 or np.sort(np.asarray(t, np.float64))[1] * W * W > 1.1
+                      for t in (tables if tables is not None else np.atleast_2d(var))):
+        return np.zeros(len(gal.x))
+    r = gal.r_e.astype(np.float64)
+    e2 = np.abs(gal.e2.astype(np.float64))
+    e = np.hypot(gal.e1.astype(np.float64), e2)
+    qmax = -KQ * r * r / (1.0 + e) ** 2 * (0.25 * (2.0 + 2.0 * e * e) + e2)
+    k = ((var[None, :] if var.ndim == 1 else var) * qmax[:, None] <= 1.0).sum(axis=1)
+    return np.where(k >= 2, k, 0).astype(np.float64)
+
+
+def flat_flops(W, kflat):
+    """FLOPs per stamp that the flat components' polynomial saves: 13 per
+    evaluation point (a scale and six FMAs) in place of 4 per component."""
+    n_eval = W * (W // 2 + 1) + (W // 2 + 1) + W + 2
+    return np.where(kflat > 0, n_eval * (4.0 * kflat - 13.0), 0.0)
+
+
 def adjoint_flops_per_stamp(W, kf, kr):
     """FLOPs the adjoint needs per stamp (FMA = 2, exp = 1): the real-to-complex
     2-D transform of the upstream gradient (2.5 W^2 log2 W^2); per evaluation
@@ -121,12 +146,24 @@ def workload_flops(gal, mix, W, adjoint=False):
     return total
 
 
+def render_flops(gal, mix, W):
+    """FLOPs that one forward launch over `gal` needs: workload_flops, which
+    counts every component by itself, less what the flat components' polynomial
+    saves."""
+    mid = np.asarray(gal.mix_id) if getattr(gal, "mix_id", None) is not None else np.zeros(len(gal.x), np.int32)
+    mid = np.broadcast_to(mid, (len(gal.x),))
+    tables = [np.asarray(mix.var[t, :int(k)], np.float64) for t, k in enumerate(mix.K)]
+    total = workload_flops(gal, mix, W)
+    for t in np.unique(mid):
+        total -= float(flat_flops(W, flat_counts(gal.subset(np.nonzero(mid == t)[0]), tables[t], W, tables)).sum())
+    return total
+
+
 def pergal_flops(gal, var, W):
-    """Algorithmic FLOPs of one forward launch whose galaxy i has its own
-    component variances var[i] (the interpolated Sersic and the bulge + disk
-    mixtures)."""
+    """FLOPs that one forward launch needs whose galaxy i has its own component
+    variances var[i] (the interpolated Sersic and the bulge + disk mixtures)."""
     kf, kr = routing_counts(gal, var, W)
-    return float(algorithmic_flops_per_stamp(W, kf, kr).sum())
+    return float((algorithmic_flops_per_stamp(W, kf, kr) - flat_flops(W, flat_counts(gal, var, W))).sum())
 
 
 def eigen_psf_flops(W, J):
@@ -172,16 +209,19 @@ def flops_roofline(flops, ms):
                 frac=round(tf / FP32_FMA_NONPACKED_TFLOPS, 4), flops_per_launch=round(flops, 1))
 
 
-def algorithmic_issue_slots(W, kf, kr):
+def algorithmic_issue_slots(W, kf, kr, kflat=0.0):
     """(VALU issue slots, exponentials) per stamp of the same algorithm when
     every FMA-able pair is one instruction: quadratic form 2 per evaluation
-    point, per Fourier component a multiply, an exponential and an FMA; 10
+    point, per Fourier component a multiply, an exponential and an FMA (the
+    kflat flat ones together: a multiply and six FMAs); 10
     per bin for phase x PSF x flux; (5/3) W^2 log2 W^2 for the inverse FFT
     with FMA butterflies (2.5 W^2 log2 W^2 FLOP at 1.5 FLOP per slot);
     per real-space component and pixel two FMAs, an exponential and an FMA."""
     H = W * (W // 2 + 1)
     n_eval = H + (W // 2 + 1) + W + 2
-    slots = n_eval * (2.0 + 3.0 * kf) + 10.0 * H + (5.0 / 3.0) * W * W * math.log2(W * W) + 4.0 * W * W * kr
+    kflat = np.broadcast_to(np.asarray(kflat, np.float64), np.shape(kf))
+    kf = kf - kflat
+    slots = n_eval * (2.0 + 3.0 * kf + 7.0 * (kflat > 0)) + 10.0 * H + (5.0 / 3.0) * W * W * math.log2(W * W) + 4.0 * W * W * kr
     exps = n_eval * kf + W * W * kr
     return slots, exps
 
@@ -562,7 +602,9 @@ def main():
     mixf = cfg["mix"].as_f32()
     amp, var = mixf.table(0)
     kf, kr = routing_counts(gal, var, W)
-    flops_stamp = algorithmic_flops_per_stamp(W, kf, kr)
+    flops_component = algorithmic_flops_per_stamp(W, kf, kr)  # every component by itself
+    kflat = flat_counts(gal, var, W)
+    flops_stamp = flops_component - flat_flops(W, kflat)
 
     cpu, oracle_stamps, refs = None, {}, {}
     if not args.no_cpu_baseline:
@@ -632,6 +674,7 @@ def main():
                     traffic=measured_traffic(),
                     kernel="render_small_kernel<64, false, false, false, false>",
                     flops_per_stamp=round(float(flops_stamp.mean()), 1),
+                    flops_per_stamp_by_component=round(float(flops_component.mean()), 1),
                     peak_note="FP32 vector FMA peak without packed instructions: 256 CU x 4 SIMD x 16 lanes x "
                               "2 FLOP x 2.4 GHz",
                     published_peak=FP32_PUBLISHED_TFLOPS,
@@ -645,16 +688,15 @@ def main():
         roofline.update(measured_peak=meas, frac_measured=round(achieved_tflops / meas, 4),
                         hbm_measured_write_gbps=probes["hbm_write_gbps"])
         # issue-slot model with the measured cost of an exponential beside two FMAs (the mixture loop's mix)
-        slots, exps = algorithmic_issue_slots(W, kf, kr)
+        slots, exps = algorithmic_issue_slots(W, kf, kr, kflat)
         c_exp = probes["exp_fma_slots_with_F_fmas"][2]
         t_model = float((slots + (c_exp - 1.0) * exps).sum()) / (meas * 1e12 / 2.0)
         roofline["issue_model"] = dict(
             slots_per_stamp=round(float(slots.mean()), 1), exps_per_stamp=round(float(exps.mean()), 1),
             exp_cost_slots=c_exp, time_ms=round(t_model * 1e3, 4),
             frac=round(t_model / (avg_kern_ms * 1e-3), 4),
-            note="time the algorithm's minimal VALU issue needs at the measured FMA rate, an exponential "
-                 "costing the measured slots beside FMAs; frac = that time / kernel time (above 1 where "
-                 "several components share a polynomial, or two wavefronts issue together)")
+            note="time the algorithm's VALU issue needs at the measured FMA rate, an exponential costing the "
+                 "measured slots beside FMAs and the flat components one polynomial; frac = that time / kernel time")
 
     parity = None
     if oracle_stamps:
@@ -948,7 +990,7 @@ def size_throughput(gfc, ctx, dev, refs, reps=5, settle=45, settle_ms=50.0):
                 par = stamp_parity(rows, [ref[j] for j, _ in keep])
                 worst.append(par)
             res[f"{cname}/W{W}"] = line(len(sub), ms, parity=par,
-                                        roofline=flops_roofline(workload_flops(sub, cfg["mix"], W), ms))
+                                        roofline=flops_roofline(render_flops(sub, cfg["mix"], W), ms))
             tot_ms += ms
             tot_n += len(sub)
             del out
@@ -973,7 +1015,7 @@ def size_throughput(gfc, ctx, dev, refs, reps=5, settle=45, settle_ms=50.0):
                reps * 4)
     res["lanczos3-dev8-64x64-100k"] = line(
         len(g), ms, parity=rows_parity("lanczos", rows),
-        roofline=flops_roofline(workload_flops(g, cfg["mix"], 64) + len(g) * lanczos_flops(64), ms))
+        roofline=flops_roofline(render_flops(g, cfg["mix"], 64) + len(g) * lanczos_flops(64), ms))
     psf.close()
     mix.close()
 
@@ -1020,7 +1062,7 @@ def size_throughput(gfc, ctx, dev, refs, reps=5, settle=45, settle_ms=50.0):
     J = len(e["comps"])
     res["eigenpsf6-dev8-64x64-100k"] = line(
         len(g), ms, parity=rows_parity("eigen", rows),
-        roofline=flops_roofline(workload_flops(g, cfg["mix"], 64) + len(g) * eigen_psf_flops(64, J), ms))
+        roofline=flops_roofline(render_flops(g, cfg["mix"], 64) + len(g) * eigen_psf_flops(64, J), ms))
     del out
     psf.close()
     mix.close()

@@ -86,3 +86,28 @@ def test_more_than_one_gpu_is_refused_with_a_message():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr and r.stdout == ""
+
+
+def test_flat_components_are_counted_as_one_polynomial():
+    # W = 16: 171 evaluation points (above).  A table of four components that
+    # are flat at every radius: 13 FLOP a point instead of 4 each
+    n_eval = 171
+    gal = wl.draw_galaxies(np.random.Generator(np.random.PCG64(2025)), 50, 16, 0, r_e_range=(0.5, 2.0))
+    flat, wide = np.full(4, 1e-6), np.array([1e-6, 0.5, 1.0])
+    one = lambda v: wl.mixture_set([(np.full(len(v), 1.0 / len(v)), v)])  # noqa: E731
+    assert (bench.flat_counts(gal, flat, 16) == 4).all()
+    assert bench.workload_flops(gal, one(flat), 16) - bench.render_flops(gal, one(flat), 16) == 50 * n_eval * 3
+    # none where a table has fewer than two such components (16 and 32), by galaxy from 64 up
+    assert (bench.flat_counts(gal, wide, 16) == 0).all()
+    assert bench.workload_flops(gal, one(wide), 16) == bench.render_flops(gal, one(wide), 16)
+    assert (bench.flat_counts(gal, flat, 32, tables=[flat, wide]) == 0).all()
+    for W in (64, 256):
+        for var in (wl.generate.exp6_table(np.random.Generator(np.random.PCG64(1)))[1], flat, wide):
+            k = bench.flat_counts(gal, var, W)
+            kf, kr = bench.routing_counts(gal, var, W)
+            assert (k != 1).all() and (k <= kf).all()
+            # the model's issue slots and exponentials follow: 3 slots and an exponential less for each, 7 more
+            s0, e0 = bench.algorithmic_issue_slots(W, kf, kr)
+            s1, e1 = bench.algorithmic_issue_slots(W, kf, kr, k)
+            pts = W * (W // 2 + 1) + (W // 2 + 1) + W + 2
+            assert np.allclose(s0 - s1, pts * (3 * k - 7 * (k > 0))) and np.allclose(e0 - e1, pts * k)
