@@ -200,7 +200,10 @@ typedef struct {
  * makes it beforehand), no device memory is allocated inside the call at
  * any W: the half spectrum stays on the chip (at W = 256 one workgroup per
  * CU renders a stamp at a time).  The same holds for the Sersic and composite
- * renders below. */
+ * renders below.  A centre's integer part is a Fourier phase like its
+ * fraction: stamps of centres that are whole pixels apart are each other's
+ * shifts to rounding, not bit for bit.  A stamp's values do not depend on the
+ * other galaxies of the call. */
 gfc_status gfc_render_stamps(gfc_ctx* ctx, gfc_psf* psf, const gfc_mix* mix,
                              const gfc_galaxies* gal, int64_t n, int W, unsigned flags,
                              float* out, void* hip_stream);

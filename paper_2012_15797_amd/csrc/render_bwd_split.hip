@@ -387,7 +387,7 @@ render_bwd_split_kernel(RenderArgs p, const float* __restrict__ gout, float* __r
     const float2 u1 = cmul(cmul(gamN, eM), pyA), u2 = cmul(cmul(gamN, eP), pyA);
     const float2 u3 = cmul(cmul(gamN, eM), pyB), u4 = cmul(cmul(gamN, eP), pyB);
     // corner twins folded into their partners (the transform is even; see the
-    // W <= 128 adjoint)
+    // W <= 32 adjoint)
     ure3[0] = u1.x + u4.x;
     uim3[0] = u1.y - u4.y;
     ure3[1] = u2.x + u3.x;

@@ -31,8 +31,8 @@
 
 namespace gfc {
 
-// Inputs of stamp g that the kernel reads per stamp, as 32-bit words:
-// x, y, flux, r_e, e1, e2, mixture id, PSF id (PT), PSF position (EIG).
+// Inputs of stamp g that the kernel reads per stamp, as 32-bit words: x, y,
+// flux, r_e, e1, e2, mixture id, PSF id (PT), PSF position (EIG), prof_a, prof_b.
 constexpr int kInWords = 12;
 
 template <bool EIG, bool PT>
@@ -136,7 +136,7 @@ __device__ __forceinline__ Galaxy read_galaxy(const uint32_t* s_gal, float* lamq
 // LZ: the Lanczos-3 sub-pixel shift (the galaxy sits at its integer position).
 //
 // Persistent: the resident workgroups (one per CU: the LDS holds one half of
-// a stamp) take stamps in turn.  Lanes 0..9 of the first wavefront load the
+// a stamp) take stamps in turn.  Lanes 0..kInWords - 1 of the first wavefront load the
 // inputs of a workgroup's next stamp while it renders the current one, so a
 // stamp starts without a memory round trip, and the first wavefront forms
 // the next stamp's galaxy for all sixteen.
@@ -581,7 +581,7 @@ __global__ void __launch_bounds__(w256::BLOCK) render_w256_kernel(RenderArgs pa)
     // pixels x = 4 r + 32 q + 0..3 (zq[0][q], then zq[1][q])
     if (rmask != 0) {
       const float dy = (float)y - G.y0 - pg[1];
-      const float dx0 = (float)(W / 2) - G.x0 - pg[0];  // dx of column W / 2, from which x counts (see the W <= 128 render)
+      const float dx0 = (float)(W / 2) - G.x0 - pg[0];  // dx of column W / 2, from which x counts (as up to 128)
       for (unsigned mk = rmask; mk != 0; mk &= mk - 1) {
         const float4 rc = s_rc[__builtin_ctz(mk)];
         const float ampr = rc.x, g = rc.y;

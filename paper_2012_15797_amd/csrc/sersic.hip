@@ -33,6 +33,7 @@ namespace {
 template <typename SetProfile>
 gfc_status render_profiles(gfc_ctx* ctx, gfc_psf* psf, const gfc_mix* mix_like, const gfc_galaxies* gal, int64_t n,
                            int W, unsigned flags, float* out, hipStream_t s, SetProfile profile) {
+  // (more stamps than any device's memory holds: 2 TB at 16 x 16)
   if (n > (int64_t)INT32_MAX) return fail(GFC_EINVAL, "at most 2^31 - 1 galaxies per call with per-galaxy mixtures");
   RenderArgs a;
   gfc_status st = fill_render_args(ctx, psf, mix_like, gal, n, W, flags, &a);
