@@ -24,16 +24,16 @@
 // The integer centre enters the phases (shift_phase), so g is never
 // rolled.
 //
-// What bounds it is VALU issue (about 4,500 instructions per wavefront and
-// stamp, 80% of the time at 64 and 128), at 256 also the barriers: there the
-// LDS holds one stamp per CU.  32 bins per thread keep it within 128 registers,
-// and half a stamp at a time within 10 KB of LDS per wavefront, so four
-// wavefronts per SIMD are resident.  Whole calls, r_e 0.5..8 px, 8 components:
-// 20,000 stamps of 64 x 64 in 173 us, 5,000 of 128 x 128 in 169 us (192 us with
-// r_e 10..60 px), 500 of 256 x 256 with r_e 10..60 px in 105 us.  One lane per
-// row and two per column with the whole g tile in LDS (two wavefronts per
-// SIMD) took 199 us at 64 and 315 us (439 us) at 128; a slab in device memory
-// took 353 us at 256.
+// Its time goes to VALU work (4,450-4,900 instructions per wavefront and
+// stamp; a wavefront waits for 31% of its time at 64, 35% at 128), at 256 also
+// to the barriers: there the LDS holds one stamp per CU.  32 bins per thread
+// keep it within 128 registers, and half a stamp at a time within 10 KB of LDS
+// per wavefront, so four wavefronts per SIMD are resident.  Whole calls, r_e
+// 0.5..8 px, 8 components: 20,000 stamps of 64 x 64 in 172 us, 5,000 of 128 x
+// 128 in 165 us (193 us with r_e 10..60 px), 500 of 256 x 256 with r_e 10..60
+// px in 105 us.  One lane per row and two per column with the whole g tile in
+// LDS (two wavefronts per SIMD) took 199 us at 64 and 315 us (440 us) at 128;
+// a slab in device memory took 353 us at 256.
 #include "bwd_common.hpp"
 #include "gfc_device.hpp"
 #include "gfc_internal.hpp"
